@@ -2428,21 +2428,25 @@ __global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end,
     }
 }
 
-// Pass 1 with the stash: copy each kept row into place.  A wavefront takes 64
-// consecutive output rows and reads each one's stash offset (kept per output
-// row) and its place from row_ptr.  Their objects are numbered in row order (a
-// prefix sum), and each lane copies every 64th of them: its row is the last
-// whose first number is at most the object's, found by a binary search over
-// the starts kept in LDS (read-only, so steps need no barrier and four are in
-// flight).  The writes are then one sequential stream per wavefront and each
-// stash row is one contiguous read; rows come out of the count pass in lattice
-// order, which is not the output's order for all-agents queries, and writing
-// rows scattered over the output costs more than reading them scattered.
+// Pass 1 with the stash: copy each kept row into place.  A wavefront takes
+// `rows` (at most 64) consecutive output rows and reads each one's stash offset
+// (kept per output row) and its place from row_ptr.  Their objects are numbered
+// in row order (a prefix sum), and each lane copies every 64th of them: its row
+// is the last whose first number is at most the object's, found by a binary
+// search over the starts kept in LDS (read-only, so steps need no barrier and
+// four are in flight).  The writes are then one sequential stream per wavefront
+// and each stash row is one contiguous read; rows come out of the count pass in
+// lattice order, which is not the output's order for all-agents queries, and
+// writing rows scattered over the output costs more than reading them scattered.
+// With few rows a group is shared by `splits` wavefronts, which take its
+// 256-object blocks in turn (the host's rule: copy_shape).
 // Rows the count pass could not keep are left to the write kernel (offset ~0).
 // When the write wants dist^2 and the stash lacks it, every kept row is walked
 // again instead, and the walk list takes query slots: then the wavefront takes
-// 64 consecutive query slots and finds each one's output row.
-__global__ __launch_bounds__(256) void gather_kernel(QArgs A, const uint4* pts, uint32_t* status) {
+// consecutive query slots and finds each one's output row (a group's first
+// wavefront lists them, the others have nothing to do).
+__global__ __launch_bounds__(256) void gather_kernel(QArgs A, const uint4* pts, uint32_t* status, uint32_t rows,
+                                                     uint32_t splits) {
     __shared__ uint32_t starts_all[4 * 64];
     const uint32_t* hdr = A.stash_hdr;
     if (hdr[kHdrMode] == 0u) return;
@@ -2452,17 +2456,20 @@ __global__ __launch_bounds__(256) void gather_kernel(QArgs A, const uint4* pts, 
     }
     const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
     uint32_t* starts = starts_all + wave * 64;
-    const uint64_t q0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + wave) * 64u;
+    const uint32_t w = blockIdx.x * (blockDim.x >> 6) + wave;
+    const uint32_t grp = w / splits, part = w - grp * splits;
+    const uint64_t q0 = (uint64_t)grp * rows;
     if (q0 >= A.Q) return;
     const uint32_t* s_ids = (const uint32_t*)A.stash_base;
     const bool has_d2 = hdr[kHdrHasD2] != 0u;
     const int64_t* s_d2 = (const int64_t*)(A.stash_base + hdr[kHdrD2Off] * (size_t)256);
     // walk again (dist^2 wanted, not stashed): by query slot; else by output row
     const bool again = A.out_d2 && !has_d2;
+    if (again && part != 0u) return;
     const uint64_t qi = q0 + lane;
     uint32_t len = 0, src = 0;
     int64_t dst = 0;
-    if (qi < A.Q) {
+    if (lane < rows && qi < A.Q) {
         // the output row: the object's id for all-agents queries (their
         // processing order is the sorted order), else the query index
         const uint32_t row = (again && A.qx == nullptr) ? pts[qi].w : (uint32_t)qi;
@@ -2492,9 +2499,9 @@ __global__ __launch_bounds__(256) void gather_kernel(QArgs A, const uint4* pts, 
     const uint64_t dbase = (uint64_t)(dst - (int64_t)excl);
     const bool want_d2 = A.out_d2 != nullptr;
     constexpr uint32_t kSteps = 4;
-    for (uint32_t cb = 0; cb < total; cb += 64u * kSteps) {
+    for (uint32_t cb = 64u * kSteps * part; cb < total; cb += 64u * kSteps * splits) {
         uint32_t v[kSteps];
-        int64_t w[kSteps], dp[kSteps];
+        int64_t d2[kSteps], dp[kSteps];
 #pragma unroll
         for (uint32_t k = 0; k < kSteps; ++k) {
             const uint32_t g = cb + 64u * k + lane;
@@ -2507,20 +2514,49 @@ __global__ __launch_bounds__(256) void gather_kernel(QArgs A, const uint4* pts, 
             const uint32_t sp = bperm(sbase, o) + g;
             dp[k] = (int64_t)(((uint64_t)bperm((uint32_t)(dbase >> 32), o) << 32) | bperm((uint32_t)dbase, o)) + g;
             v[k] = 0u;
-            w[k] = 0;
+            d2[k] = 0;
             if (g < total) {
                 v[k] = s_ids[sp];
-                if (want_d2) w[k] = s_d2[sp];
+                if (want_d2) d2[k] = s_d2[sp];
             }
         }
 #pragma unroll
         for (uint32_t k = 0; k < kSteps; ++k) {
             if (cb + 64u * k + lane < total) {
                 A.out_ids[dp[k]] = v[k];
-                if (want_d2) A.out_d2[dp[k]] = w[k];
+                if (want_d2) A.out_d2[dp[k]] = d2[k];
             }
         }
     }
+}
+
+// Rows per wavefront and wavefronts per group of rows of the stash copy.  A
+// wavefront's objects go in dependent rounds of 256 (a load latency each), so
+// what matters is that one wavefront's rounds stay few while the chip holds
+// every wavefront at once: kCopyWaves of them (32 per CU), from one row each,
+// shared by up to 8 wavefronts, for a service's small batch (rows of up to
+// thousands of pairs) to 64 rows each for an all-objects step.  With 64 rows
+// per wavefront whatever the batch, the copy of 214 mixed rows took 130 us on
+// four wavefronts and that of 65,536 rows (20 M pairs) 219 us; by this rule
+// the batch of 214 went from 279 to 138 us in all and that of 65,536 from
+// 1,410 to 1,261 (1,406, 1,330, 1,285, 1,261, 1,260, 1,260 us at 1, 2, 4, 8,
+// 16 and 32 K wavefronts).
+constexpr uint32_t kCopyWaves = 8192;
+struct CopyShape {
+    uint32_t rows, splits;
+};
+CopyShape copy_shape(uint32_t Q) {
+    CopyShape c{1u, 1u};
+    while (c.rows < 64u && (uint64_t)Q > (uint64_t)kCopyWaves * c.rows) c.rows *= 2u;
+    while (c.splits < 8u && (uint64_t)Q * c.splits * 2u <= kCopyWaves) c.splits *= 2u;
+    return c;
+}
+
+hipError_t launch_copy(const QArgs& q, const LatArgs& L, hipStream_t st) {
+    const CopyShape c = copy_shape(q.Q);
+    const uint64_t waves = (((uint64_t)q.Q + c.rows - 1) / c.rows) * c.splits;
+    gather_kernel<<<(uint32_t)((waves + 3) / 4), 256, 0, st>>>(q, L.pts, L.status, c.rows, c.splits);
+    return hipGetLastError();
 }
 
 // Kernel choice by variant: cube, sphere, sphere with the row table in LDS;
@@ -2748,8 +2784,7 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
     if (q.mode != SPHIDX_MODE_KNN) {
         if ((e = mark(ev_begin)) != hipSuccess) return e;
         // rows kept by a stashing count pass (does nothing otherwise)
-        gather_kernel<<<(q.Q + 255) / 256, 256, 0, st>>>(q, L.pts, L.status);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_copy(q, L, st)) != hipSuccess) return e;
         e = launch_ptr(either ? SPHIDX_PICK(write_kernel, variant, kEither, , false)
                               : SPHIDX_PICKP(write_kernel, variant, kSphere, , false),
                        q.Q, q, w, b, sh1, st, L, T);
@@ -2777,8 +2812,7 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
     }
     if ((e = mark(ev_begin)) != hipSuccess) return e;
     // rows kept by the count pass (does nothing otherwise), then the rest
-    gather_kernel<<<(q.Q + 255) / 256, 256, 0, st>>>(q, L.pts, L.status);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_copy(q, L, st)) != hipSuccess) return e;
     e = launch_ptr(SPHIDX_PICKP(topm_kernel, variant, kEither, , false), q.Q, q, w, b, sh2, st, L, T);
     return e == hipSuccess ? mark(ev_end) : e;
 }
