@@ -174,8 +174,11 @@ __device__ __forceinline__ uint64_t sq(uint32_t g) { return (uint64_t)g * (uint6
 // stored in descriptor word 12 (an upper bound of its K-th distance; sphere
 // walks only, which leave that word unused).  F_LONG: a radius row expected
 // to be longer than a wavefront's buffer, counted and kept one block per row.
+// F_WINDOW: a radius row that the block kernel of the write pass left to the
+// windowed top-M kernel.
 enum : uint32_t {
-    F_VALID = 1u, F_KNN = 2u, F_SPHERE = 4u, F_OUTSIDE = 8u, F_LIST = 16u, F_KBOUND = 32u, F_LONG = 64u
+    F_VALID = 1u, F_KNN = 2u, F_SPHERE = 4u, F_OUTSIDE = 8u, F_LIST = 16u, F_KBOUND = 32u, F_LONG = 64u,
+    F_WINDOW = 128u
 };
 
 struct Query {
@@ -2132,7 +2135,7 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
         const uint32_t rowlen = (uint32_t)(A.row_ptr[s.row + 1] - rb);
         if (rowlen == 0 || !(s.flags & F_VALID)) return;
         // long radius rows the block-per-row kernel takes
-        if (FROM_LIST && A.long_waves > 1 && !(s.flags & F_KNN) && rowlen <= kLongCap) return;
+        if (FROM_LIST && A.long_waves > 1 && !(s.flags & (F_KNN | F_WINDOW))) return;
         uint64_t* td = tdA;
         uint64_t* ud = tdB;
         uint32_t* tix = tiA;
@@ -2278,10 +2281,12 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum) 
 }
 
 // Sort the block's n <= kLongCap pairs (td, ti) by (dist^2, id) and store
-// them at dst; every pair has dist^2 <= r2.  The pairs stay where they are:
-// the bucket pass orders their indices (sx), which the rank pass follows.
+// them at dst; a pair holds its dist^2 less `base`, at most r2.  The pairs
+// stay where they are: the bucket pass orders their indices (sx), which the
+// rank pass follows.
 __device__ void block_sort_store(const uint64_t* td, const uint32_t* ti, uint32_t* sx, uint32_t* hist,
-                                 uint32_t* wsum, uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2) {
+                                 uint32_t* wsum, uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2,
+                                 uint64_t base = 0) {
     const uint32_t tid = threadIdx.x, nt = blockDim.x;
     const float scale = r2 > 0 ? (float)n / (float)r2 : 0.0f;
     for (uint32_t t = tid; t < n; t += nt) hist[t] = 0u;
@@ -2317,8 +2322,107 @@ __device__ void block_sort_store(const uint64_t* td, const uint32_t* ti, uint32_
             rank += key_less(td[o], ti[o], d, id) ? 1u : 0u;
         }
         dst_ids[rank] = id;
-        if (dst_d2) dst_d2[rank] = (int64_t)d;
+        if (dst_d2) dst_d2[rank] = (int64_t)(d + base);
     }
+}
+
+// A radius row of more than kLongCap pairs, by one block in two walks (write
+// pass): the first counts its hits per distance bucket (dist^2 >> sh, sh such
+// that r^2 falls below kShellBuckets), the second writes each hit's sorted
+// position into the row's own output, grouped by bucket; then runs of buckets
+// of at most kShellCap pairs (shells, centre to edge) are read back into LDS,
+// their objects' distances computed again, ordered by the block sort and
+// stored in place.  The row needs no memory but its output.  Returns false,
+// with nothing written, when one bucket alone holds more than kShellCap pairs
+// (many objects at one distance): such a row is left to the windowed kernel.
+// What bounds it is the walk's and the block sort's instruction issue and LDS
+// traffic.  Before, every such row took one window of sort_cap pairs after
+// another on one wavefront, each window walking the whole row again: 512 rows
+// of about 20,000 pairs (20 objects per cell, 7 cells, clipped 32^3) took
+// 103 ms in all; now 0.65 ms.
+constexpr uint32_t kShellCap = 2560, kShellBuckets = 2048;
+
+template <int METHOD>
+__device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, const AxisWrap& aw, const Query& s,
+                          int64_t rb, uint32_t rowlen, uint64_t* td, uint32_t* ti, uint32_t* sx, uint32_t* hist,
+                          uint32_t* bkt, uint32_t* own, uint32_t* ctl) {
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, wave = tid >> 6, nw = nt >> 6;
+    const uint32_t rbits = s.r2 ? 64u - (uint32_t)__builtin_clzll(s.r2) : 0u;
+    const uint32_t sh = rbits > 11u ? rbits - 11u : 0u;  // kShellBuckets = 2^11
+    uint32_t cand = 0, walked = 0;
+    auto walk_row = [&](auto&& visit) {
+        walk<METHOD, false, false>(L, T, nullptr, s, false, walked, [&]() { return s.r2; },
+                                   [&](const RowRef& r) -> bool {
+            return for_candidates(L, r.st0, r.cnt0, r.st1, r.cnt1, own, cand, visit);
+        }, 64u * wave, 64u * nw);
+    };
+    for (uint32_t t = tid; t < kShellBuckets; t += nt) bkt[t] = 0u;
+    if (tid == 0) ctl[3] = 0u;
+    __syncthreads();
+    walk_row([&](bool act, uint32_t p, const uint4& P) -> bool {
+        const uint64_t d2 = obj_dist2(aw, s, P);
+        if (act && d2 <= s.r2 && p != s.self) atomicAdd(&bkt[(uint32_t)(d2 >> sh)], 1u);
+        return false;
+    });
+    __syncthreads();
+    {
+        // bucket starts, each thread owning a run of buckets
+        const uint32_t per = kShellBuckets / nt, b0 = tid * per;
+        uint32_t sum = 0, most = 0;
+        for (uint32_t k = 0; k < per; ++k) {
+            sum += bkt[b0 + k];
+            most = max(most, bkt[b0 + k]);
+        }
+        if (most > kShellCap) ctl[3] = 1u;
+        uint32_t run = block_scan_excl(sum, ctl + 4);
+        for (uint32_t k = 0; k < per; ++k) {
+            const uint32_t c = bkt[b0 + k];
+            bkt[b0 + k] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    if (ctl[3]) return false;
+    uint32_t* pos = A.out_ids + rb;
+    walk_row([&](bool act, uint32_t p, const uint4& P) -> bool {
+        const uint64_t d2 = obj_dist2(aw, s, P);
+        if (act && d2 <= s.r2 && p != s.self) {
+            const uint32_t t = atomicAdd(&bkt[(uint32_t)(d2 >> sh)], 1u);
+            if (t < rowlen) pos[t] = p;
+        }
+        return false;
+    });
+    // (the block's own stores, seen by all of it after the barrier; each
+    // bucket's cursor now ends at the next one's start)
+    __syncthreads();
+    for (uint32_t b = 0, t0 = 0; t0 < rowlen;) {
+        // the shell: buckets b .. e - 1, as many as fit
+        uint32_t lo = b + 1u, hi = kShellBuckets;  // the least e, the most
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1u) >> 1;
+            if (bkt[mid - 1u] - t0 <= kShellCap)
+                lo = mid;
+            else
+                hi = mid - 1u;
+        }
+        const uint32_t e = lo, n = min(bkt[e - 1u], rowlen) - t0;
+        const uint64_t base = (uint64_t)b << sh;
+        const uint64_t span = min(s.r2, ((uint64_t)e << sh) - 1ull) - base;
+        for (uint32_t t = tid; t < n; t += nt) {
+            const uint4 P = L.pts[pos[t0 + t]];
+            td[t] = obj_dist2(aw, s, P) - base;
+            ti[t] = P.w;
+        }
+        __syncthreads();
+        if (n > 0)
+            block_sort_store(td, ti, sx, hist, ctl + 4, n, span, A.out_ids + rb + t0,
+                             A.out_d2 ? A.out_d2 + rb + t0 : nullptr, base);
+        __syncthreads();
+        t0 += n;
+        b = e;
+        if (e >= kShellBuckets) break;
+    }
+    return true;
 }
 
 // COUNT: the count pass's form.  The rows come from the list of rows the
@@ -2336,6 +2440,7 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
     uint32_t* ctl = hist + kLongCap;  // [0] hits so far, [1] list entry taken, [2] stash offset, [4, 12) wave sums
     const uint32_t wave = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = lane_id();
     uint32_t* own = ctl + 16 + wave * 64;
+    static_assert(kShellCap * 20 + kShellBuckets * 4 <= kLongCap * 20, "a shell's buffers fit the row's");
     if (!COUNT && A.row_ptr[A.Q] > A.capacity) return;  // (the write kernel sets the flag)
     const AxisWrap aw = axis_wrap(L);
     const uint32_t nq = uni(*A.list_count);
@@ -2356,6 +2461,16 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
         if (!COUNT) {
             rb = A.row_ptr[s.row];
             rowlen = (uint32_t)(A.row_ptr[s.row + 1] - rb);
+        }
+        if (!COUNT && rowlen > kLongCap && (s.flags & (F_VALID | F_KNN | F_WINDOW)) == F_VALID) {
+            uint32_t* sti = (uint32_t*)(td + kShellCap);
+            uint32_t* ssx = sti + kShellCap;
+            uint32_t* shist = ssx + kShellCap;
+            if (!shell_row<METHOD>(L, T, A, aw, s, rb, rowlen, td, sti, ssx, shist, shist + kShellCap, own, ctl) &&
+                threadIdx.x == 0)
+                ((uint32_t*)(A.desc + 4 * (size_t)qi))[6] = s.flags | F_WINDOW;
+            __syncthreads();
+            continue;
         }
         // the same for every wave of the block
         const bool mine = (s.flags & F_VALID) && !(s.flags & F_KNN) && rowlen > 0 && rowlen <= kLongCap;
