@@ -244,6 +244,7 @@ QArgs q_args(const sphidx_queries* q, sphidx_csr* csr, const Launch& ln) {
     A.stash_hdr = lists + 3 * SPHIDX_QSTRIDE;
     A.xq_count = lists + 4 * SPHIDX_QSTRIDE;
     A.lq_count = lists + 5 * SPHIDX_QSTRIDE;
+    A.item_count = lists + 6 * SPHIDX_QSTRIDE;
     A.stash_ctr = lists + SPHIDX_NLISTS * SPHIDX_QSTRIDE;
     A.longq = (uint32_t*)(ws + ql.longq);
     A.fbq = (uint32_t*)(ws + ql.fbq);

@@ -37,6 +37,8 @@
 // III.B, III.C) or of their estimated work finds smallest; a list entry is
 // one more kind of row.
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 #include "sphidx_internal.h"
 
@@ -54,8 +56,8 @@ constexpr int kSphere = 0, kCube = 1, kEither = 2, kPaper = 3;
 __device__ __forceinline__ uint32_t lane_id() {
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t base = 0u) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
 }
 __device__ __forceinline__ uint32_t bperm(uint32_t v, uint32_t lane) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)v);
@@ -221,9 +223,12 @@ __host__ __device__ inline float knn_target(float k) {
     return a < b ? a : b;
 }
 
+// Every query; with the tile kernel, the objects outside the region only (a
+// row that kernel does not keep is set up where it is walked, tile_query).
 template <int METHOD>
 __global__ __launch_bounds__(256) void setup_kernel(LatArgs L, TabArgs T, QArgs A) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t first = A.tiles ? L.cs[L.ncells] : 0u, stride = gridDim.x * blockDim.x;
+    for (uint32_t i = first + blockIdx.x * blockDim.x + threadIdx.x; uni(i) < A.Q; i += stride) {
     bool range_bad = false, fallback = false, to_list = false, longrow = false;
     if (i < A.Q) {
         uint32_t q[3], row, r, k;
@@ -435,6 +440,7 @@ __global__ __launch_bounds__(256) void setup_kernel(LatArgs L, TabArgs T, QArgs 
     }
     if (__ballot(range_bad) && lane_id() == 0) atomicOr(L.status, SPHIDX_FLAG_RANGE);
     if (__ballot(fallback) && lane_id() == 0) atomicOr(L.status, SPHIDX_FLAG_FALLBACK);
+    }
 }
 
 // Descriptors are read through the scalar cache (the address is uniform and
@@ -472,6 +478,33 @@ __device__ __forceinline__ Query load_query(const LatArgs& L, const QArgs& A, ui
         s.dn[a] = s.f[a] + 1u;
     }
     s.r2 = (uint64_t)s.r * (uint64_t)s.r;
+    return s;
+}
+
+// The query of sorted position qi, an object of the region, after a count pass
+// by tiles (one radius, on the sphere tables): what setup_kernel would have
+// made of it.
+__device__ __forceinline__ Query tile_query(const LatArgs& L, const TabArgs& T, const QArgs& A, uint32_t qi) {
+    Query s;
+    const const_u32* P = (const const_u32*)(L.pts + uni(qi));
+    s.row = P[3];
+    s.r = A.rad_u;
+    s.r2 = (uint64_t)s.r * (uint64_t)s.r;
+    s.k = s.ncube = s.kbr = 0u;
+    s.flags = F_VALID | F_SPHERE;
+    const uint32_t e = 1u << L.F;
+    for (int a = 0; a < 3; ++a) {
+        s.q[a] = P[a];
+        s.c[a] = s.q[a] >> L.F;
+        s.f[a] = s.q[a] & (e - 1u);
+        s.up[a] = e - s.f[a];
+        s.dn[a] = s.f[a] + 1u;
+        if (!((L.cyc >> a) & 1u) && ((s.q[a] + s.r) >> L.F) >= (1u << L.lg[a])) s.flags |= F_OUTSIDE;
+    }
+    const uint32_t cls = (s.f[1] >> (L.F - T.s)) | ((s.f[2] >> (L.F - T.s)) << T.s);
+    s.tb = T.cstart[cls];
+    s.tend = T.rindex[(size_t)cls * T.nr + ((s.r + (1u << T.rshift) - 1u) >> T.rshift)];
+    s.self = (A.flags & SPHIDX_EXCLUDE_SELF) ? qi : kMaxId;
     return s;
 }
 
@@ -635,15 +668,14 @@ __device__ __forceinline__ RowRef row_ranges(const LatArgs& L, uint32_t base, in
 
 // Cells in x order (objects inside each cell by x, cells of a row in x
 // order): the objects of a plain run have increasing x, and those within the
-// sphere's x-slab [qx - X, qx + X] on this row are one sub-range, found by
+// sphere's x-slab [lo_t, hi_t] on this row are one sub-range, found by
 // two binary searches on x (interleaved, so that their loads overlap).  Only
 // for rows with many objects, where the searches cost less than testing the
 // objects outside the slab.
 constexpr uint32_t kNarrowMin = 24;
 
-__device__ __forceinline__ void narrow_x(const LatArgs& L, RowRef& r, uint32_t qx, uint32_t X) {
+__device__ __forceinline__ void narrow_x(const LatArgs& L, RowRef& r, uint32_t lo_t, uint32_t hi_t) {
     const uint32_t* xs = (const uint32_t*)L.pts;  // x of sorted position p at xs[4 p]
-    const uint32_t lo_t = qx > X ? qx - X : 0u, hi_t = qx + X;
     uint32_t a = r.st1, na = r.cnt1, b = r.st1, nb = r.cnt1;
     while (na | nb) {
         if (na) {
@@ -721,7 +753,8 @@ __device__ __forceinline__ RowRef sphere_row(const LatArgs& L, const Query& s, u
     }
     const uint32_t base = (tz << (L.lg[0] + L.lg[1])) | (ty << L.lg[0]);
     RowRef rr = row_ranges(L, base, (int)s.c[0] - nneg, (int)s.c[0] + npos, ia, ib, live);
-    if (L.xsorted && rr.plain && rr.cnt1 >= kNarrowMin && *L.xsorted) narrow_x(L, rr, s.q[0], X);
+    if (L.xsorted && rr.plain && rr.cnt1 >= kNarrowMin && *L.xsorted)
+        narrow_x(L, rr, s.q[0] > X ? s.q[0] - X : 0u, s.q[0] + X);
     return rr;
 }
 
@@ -2028,6 +2061,698 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
 }
 
 // ---------------------------------------------------------------------------
+// Pass 0, all-agents queries of one radius by tiles of space: a wavefront
+// takes up to 16 queries that lie close together, reads the candidates of all
+// of them once, and tests every pair on the matrix cores.
+//
+// Queries are ordered for this by strips: a strip is 2^wy x 2^wz rows of
+// cells along x, cut into chunks of 2^cl columns; a chunk's queries, column
+// by column, go to work items (tile_items_kernel) and, inside an item, to
+// groups of up to 16.  A group's candidates are the objects within the radius
+// of the box around its queries: one lane per x-row of cells solves the row's
+// run, the runs' objects are spread over the lanes, and those within reach of
+// the box go to a ring in LDS as coordinates relative to the group's first
+// query.
+//
+// 64 candidates at a time leave the ring, one per lane, as x, y, z and
+// x^2 + y^2 + z^2 in double precision; eight lane-row swaps turn them into the
+// operands of four v_mfma_f64_16x16x4.  With the queries' [-2x, -2y, -2z, 1]
+// as rows and the accumulator starting at 2^52 + slot 2^d + |q|^2, every
+// element is 2^52 + slot 2^d + dist^2: all operands and sums are integers
+// below 2^53, so the result is exact whatever the order of the sum, its low 52
+// bits are the integer (slot, dist^2), and a hit is one comparison with
+// 2^52 + slot 2^d + r^2.  Hits go to LDS as 64-bit keys (slot, dist^2, id);
+// one bucket sort, its keys held in registers and put in place, orders the
+// group's rows.
+//
+// Bound by instruction issue (VALU 66 % busy on the 8.4 M-agent timestep, the
+// rest waits on LDS at the 12 wavefronts a CU holds).  Against a row walk per
+// query (group_count_kernel) a query pays a sixteenth of its group's rows and
+// candidate loads, and a pair a comparison instead of an address search, three
+// wrapped differences and three products; in exchange it is tested against
+// the whole group's candidates (about 310 for 57 hits at r = 3 cells and 0.5
+// objects per cell, instead of 109).  There: 172 VALU instructions per query
+// instead of 371, count kernel 5.60 -> 3.35 ms.  With the ring holding
+// doubles, hits placed one by one, ranks from loops over each key's bucket and
+// the descriptors read it took 6.0 ms; 128-register variants spill (5.3 ms),
+// groups of 8 queries took the same time at twice the rows.
+
+// queries per group, pairs of its hit buffer, rows per chunk of the walk,
+// candidates of the ring (a power of two, at least 63 + 64), cells per strip
+// chunk, queries per work item
+constexpr uint32_t kTileQ = 16, kTileHits = 960, kTileRows = 88, kTileRing = 128;
+constexpr uint32_t kTileCellLayers = 4, kTileCells = 64 * kTileCellLayers;
+constexpr uint32_t kTileBuckets = 64;  // sort buckets per query slot
+constexpr uint32_t kTileNear = 8;      // places a key can be from its rank in bucket order without the slow path
+// LDS of a block (one wavefront): hit keys and a spare one; then ring, row
+// records and owner marks, all free once the tests are done, when the sort's
+// bucket counts take their place.  (kTileHits / 64 odd: a lane's run of keys
+// then starts in another bank than its neighbours'.)
+constexpr uint32_t kTileScratch = 4112;
+constexpr uint32_t kTileLds = (kTileHits + 2) * 8 + kTileScratch;
+static_assert(kTileScratch >= (kTileQ * kTileBuckets + 1) * 4, "the bucket counts fit the walk's buffers");
+static_assert(kTileScratch >= kTileRing * 16 + kTileRows * 12 + 256, "the walk's buffers fit");
+static_assert(kTileRows <= 254, "owner marks hold a row + 1 in one byte");
+
+constexpr uint32_t kTileLayers = (kTileRows + 63) / 64;
+
+struct TileArgs {
+    uint32_t cl, wy, wz;    // log2 of a chunk's columns and of a strip's rows in y and z
+    uint32_t nchunks;
+    uint32_t part;          // queries per work item (a multiple of kTileQ)
+    uint32_t d2bits;        // bits of dist^2 in a key: those of the largest r^2
+};
+
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+// First cell of row `row` of a chunk.
+__device__ __forceinline__ uint32_t tile_cell(const LatArgs& L, const TileArgs& TA, uint32_t chunk, uint32_t row,
+                                              uint32_t col) {
+    const uint32_t lx = L.lg[0] - TA.cl, ly = L.lg[1] - TA.wy;
+    const uint32_t cx = chunk & ((1u << lx) - 1u), sy = (chunk >> lx) & ((1u << ly) - 1u), sz = chunk >> (lx + ly);
+    const uint32_t y = (sy << TA.wy) + (row & ((1u << TA.wy) - 1u)), z = (sz << TA.wz) + (row >> TA.wy);
+    return pack_cell(L, (cx << TA.cl) + col, y, z);
+}
+
+// Queries per work item of a chunk of T queries: a multiple of kTileQ, at
+// most 1,024 items per chunk.
+__device__ __forceinline__ uint32_t tile_part(const TileArgs& TA, uint32_t T) {
+    const uint32_t per = (T + 1023u) >> 10;
+    return max(TA.part, (per + kTileQ - 1u) & ~(kTileQ - 1u));
+}
+
+// One thread per chunk: its work items, chunk | part << 22.  The objects left out
+// by the build, after every cell, get empty rows here.
+__global__ __launch_bounds__(256) void tile_items_kernel(LatArgs L, QArgs A, TileArgs TA, uint32_t* items,
+                                                         uint32_t* count) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint32_t i = L.cs[L.ncells + 1] + c; i < L.n; i += gridDim.x * blockDim.x) {
+        const uint32_t row = L.pts[i].w;
+        A.row_ptr[row] = 0;
+        if (A.stash) A.soff[row] = 0u;
+    }
+    uint32_t T = 0;
+    if (c < TA.nchunks) {
+        for (uint32_t row = 0; row < (1u << (TA.wy + TA.wz)); ++row) {
+            const uint32_t cell = tile_cell(L, TA, c, row, 0u);
+            T += L.cs[cell + (1u << TA.cl)] - L.cs[cell];
+        }
+    }
+    const uint32_t part = tile_part(TA, T), n = (T + part - 1u) / part;
+    const uint32_t incl = scan_add(n), total = lane_val(incl, 63);
+    uint32_t base = 0;
+    if (total > 0 && lane_id() == 0) base = atomicAdd(count, total);
+    base = uni(base) + incl - n;
+    for (uint32_t k = 0; k < n; ++k) items[base + k] = c | (k << 22);
+}
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+// Minimum and maximum over the 16 lanes of a DPP row (rotations).
+__device__ __forceinline__ int row_min(int v) {
+    v = min(v, dpp_i<0x128>(v));
+    v = min(v, dpp_i<0x124>(v));
+    v = min(v, dpp_i<0x122>(v));
+    return min(v, dpp_i<0x121>(v));
+}
+__device__ __forceinline__ int row_max(int v) {
+    v = max(v, dpp_i<0x128>(v));
+    v = max(v, dpp_i<0x124>(v));
+    v = max(v, dpp_i<0x122>(v));
+    return max(v, dpp_i<0x121>(v));
+}
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) {
+    v += (uint32_t)dpp_i<0x128>((int)v);
+    v += (uint32_t)dpp_i<0x124>((int)v);
+    v += (uint32_t)dpp_i<0x122>((int)v);
+    return v + (uint32_t)dpp_i<0x121>((int)v);
+}
+
+// Rows 2, 3 of a's 16-lane rows change places with rows 0, 1 of b; rows 1, 3
+// of a with rows 0, 2 of b.
+__device__ __forceinline__ void swap_rows32(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void swap_rows16(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void swap_rows32(double& a, double& b) {
+    uint32_t ah = (uint32_t)__double2hiint(a), al = (uint32_t)__double2loint(a);
+    uint32_t bh = (uint32_t)__double2hiint(b), bl = (uint32_t)__double2loint(b);
+    swap_rows32(ah, bh);
+    swap_rows32(al, bl);
+    a = __hiloint2double((int)ah, (int)al);
+    b = __hiloint2double((int)bh, (int)bl);
+}
+__device__ __forceinline__ void swap_rows16(double& a, double& b) {
+    uint32_t ah = (uint32_t)__double2hiint(a), al = (uint32_t)__double2loint(a);
+    uint32_t bh = (uint32_t)__double2hiint(b), bl = (uint32_t)__double2loint(b);
+    swap_rows16(ah, bh);
+    swap_rows16(al, bl);
+    a = __hiloint2double((int)ah, (int)al);
+    b = __hiloint2double((int)bh, (int)bl);
+}
+
+// This lane's bit of a wave mask, as a predicate.
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// v plus this lane's bit of a wave mask (one add with the mask as carry).
+__device__ __forceinline__ uint32_t add_bit(uint32_t v, uint64_t m) {
+    uint32_t r;
+    uint64_t carry;
+    asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(r), "=s"(carry) : "v"(v), "s"(m));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t sub_bit(uint32_t v, uint64_t m) {
+    uint32_t r;
+    uint64_t borrow;
+    asm("v_subb_co_u32 %0, %1, %2, 0, %3" : "=v"(r), "=s"(borrow) : "v"(v), "s"(m));
+    return r;
+}
+// The next lane's value (lane 63: all ones).
+__device__ __forceinline__ uint64_t next_lane(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)(uint32_t)v, 0x130, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)(uint32_t)(v >> 32), 0x130, 0xF, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// STASH: rows are sorted and kept; else counted only.  EXCL: an object's own
+// entry is left out.
+template <bool STASH, bool EXCL>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void tile_count_kernel(LatArgs L, QArgs A,
+                                                                                                 TileArgs TA) {
+    extern __shared__ __align__(16) char smem[];
+    uint32_t lane = lane_id();
+    uint64_t* hb = (uint64_t*)smem;
+    char* sc = smem + (kTileHits + 2) * 8;
+    uint4* ring = (uint4*)sc;                            // kTileRing candidates: x, y, z relative, id
+    uint2* rpos = (uint2*)(sc + kTileRing * 16);         // kTileRows: position bases of a row's two ranges,
+    uint32_t* rbnd = (uint32_t*)(rpos + kTileRows);      // and the candidate slot where the second starts
+    uint32_t* own = rbnd + kTileRows;                    // 64
+    uint32_t* hh = (uint32_t*)sc;                        // the sort's bucket counts
+    ulonglong2* slotd = (ulonglong2*)hb;                 // per slot: accumulator start, threshold (before the tests)
+    const AxisWrap aw = axis_wrap(L);
+    const uint32_t d2b = TA.d2bits, sh = 60u - d2b;      // key: slot (4 bits) | dist^2 (d2b) | id (sh)
+    const uint32_t region = blockIdx.x % SPHIDX_NREGION;
+    const uint32_t F = L.F, E1 = (1u << F) - 1u;
+    const int R = (int)A.rad_u;
+    // conservative single-precision reach (a candidate set only: every pair is
+    // tested exactly)
+    const float R2f = (float)R * (float)R * 1.000002f + 1.0f;
+    // bucket of a key in its slot: floor(64 v / (v_max + 1)), v the top 24 bits
+    // of dist^2: monotone in dist^2
+    const float scale = (float)kTileBuckets / ((float)((((uint64_t)A.rad_u * A.rad_u) << sh) >> 36) + 1.0f);
+    uint32_t cur = 0, lim = 0;
+    bool dry = false;
+    uint32_t nlim = kTileQ;  // queries per group (fewer where hits overflow the buffer)
+    const uint32_t ncell = 1u << (TA.cl + TA.wy + TA.wz);
+    const uint32_t rowmask = (1u << (TA.wy + TA.wz)) - 1u;
+    for_each_range(uni(*A.item_count), A, queue_set(A, kQCount), [&](uint32_t ib, uint32_t ie) {
+        for (uint32_t it = ib; it < ie; ++it) {
+            const uint32_t item = uni(A.longq[it]);
+            const uint32_t chunk = item & 0x3FFFFFu, part = item >> 22;
+            // ---- the chunk's cells, column by column, four per lane: the
+            // ranks of their queries and the position of rank 0
+            uint32_t cex[kTileCellLayers], cin[kTileCellLayers], cst[kTileCellLayers], total_q = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < kTileCellLayers; ++k) {
+                const uint32_t c = k * 64u + lane;
+                cin[k] = cst[k] = 0;
+                if (c < ncell) {
+                    const uint32_t cell = tile_cell(L, TA, chunk, c & rowmask, c >> (TA.wy + TA.wz));
+                    cst[k] = L.cs[cell];
+                    cin[k] = L.cs[cell + 1u] - cst[k];
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kTileCellLayers; ++k) {
+                const uint32_t n = cin[k];
+                cin[k] = total_q + scan_add(n);
+                cex[k] = cin[k] - n;
+                cst[k] -= cex[k];
+                total_q = lane_val(cin[k], 63);
+            }
+            const uint32_t per = tile_part(TA, total_q);
+            const uint32_t rend = min(total_q, (part + 1u) * per);
+            uint32_t r0 = part * per, ng = 0;
+            // ---- the group from rank r0 (groups of equal size): lane l takes
+            // its query l mod 16 (the last one's record past the end); a cell
+            // leaves its position base at its first rank in the group, and
+            // every rank takes the last one before it
+            uint32_t pos = 0;
+            auto group = [&]() -> uint4 {
+                const uint32_t slot = lane & 15u;
+                ng = (rend - r0 + nlim - 1u) / nlim;
+                ng = (rend - r0 + ng - 1u) / ng;
+                wave_sync();
+                if (lane < 16u) own[lane] = 0u;
+                wave_sync();
+#pragma unroll
+                for (uint32_t k = 0; k < kTileCellLayers; ++k)
+                    if (cin[k] > cex[k] && cex[k] < r0 + ng && cin[k] > r0) {
+                        const uint32_t w = cex[k] > r0 ? cex[k] - r0 : 0u;
+                        own[w] = w + 1u;
+                        own[16u + w] = cst[k];
+                    }
+                wave_sync();
+                uint32_t first = own[slot];
+                first = max(first, (uint32_t)dpp_i<0x111>((int)first));
+                first = max(first, (uint32_t)dpp_i<0x112>((int)first));
+                first = max(first, (uint32_t)dpp_i<0x114>((int)first));
+                first = max(first, (uint32_t)dpp_i<0x118>((int)first));
+                pos = own[15u + max(first, 1u)] + r0 + min(slot, ng - 1u);
+                wave_sync();
+                return L.pts[pos];
+            };
+            uint4 Q = make_uint4(0, 0, 0, 0);
+            if (r0 < rend) Q = group();
+            while (r0 < rend) {
+                // (what follows from the lane is made again for each group: kept
+                // over all of them it would not fit the registers)
+                asm volatile("" : "+v"(lane));
+                const uint32_t slot = lane & 15u, quad = lane >> 4;
+                const bool mine = slot < ng;
+                const uint32_t row = Q.w, qpos = pos;
+                uint32_t hcount = 0;  // hits of the group
+                // ---- the box around the queries, relative to the first
+                const uint32_t o[3] = {uni(Q.x), uni(Q.y), uni(Q.z)};
+                const uint32_t qv[3] = {Q.x, Q.y, Q.z};
+                int q3[3], lo[3], hi[3];
+                bool outside = false;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    // (slots past the end repeat the last query)
+                    q3[a] = (int)(((qv[a] - o[a]) + aw.half[a]) & aw.mask[a]) - (int)aw.half[a];
+                    lo[a] = (int)uni((uint32_t)row_min(q3[a]));
+                    hi[a] = (int)uni((uint32_t)row_max(q3[a]));
+                    outside = outside || (!((L.cyc >> a) & 1u) && (((int)o[a] + hi[a] + R) >> (F + L.lg[a])) != 0);
+                }
+                const double qx = q3[0], qy = q3[1], qz = q3[2];
+                const double bias = (double)((uint64_t)slot << d2b) + 4503599627370496.0;
+                const double cq = __builtin_fma(qx, qx, __builtin_fma(qy, qy, __builtin_fma(qz, qz, bias)));
+                const double tq = mine ? __builtin_fma((double)R, (double)R, bias) : 0.0;
+                const double fa = quad == 0u ? -2.0 * qx : quad == 1u ? -2.0 * qy : quad == 2u ? -2.0 * qz : 1.0;
+                // accumulator starts and thresholds of this lane's four rows,
+                // slots quad + 4 i
+                if (lane < kTileQ)
+                    slotd[lane] = make_ulonglong2((uint64_t)__double_as_longlong(cq), (uint64_t)__double_as_longlong(tq));
+                wave_sync();
+                dbl4 C, thr;
+                uint32_t selfp[4] = {kMaxId, kMaxId, kMaxId, kMaxId};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const ulonglong2 w = slotd[quad + 4u * i];
+                    C[i] = __longlong_as_double((long long)w.x);
+                    thr[i] = __longlong_as_double((long long)w.y);
+                    if (EXCL) selfp[i] = bperm(row, quad + 4u * i);
+                }
+                wave_sync();
+                uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+                uint32_t head = 0, fill = 0;  // ring: first pending entry, entries pending
+                // 64 pending candidates, one per lane (nb of them; the rest
+                // padding that is never within a radius): their four operand
+                // rows are transposed between the lanes' 16-lane rows, so that
+                // tile t's operand holds component k of candidate 16 t + column
+                // in row k
+                auto batch = [&](uint32_t nb) {
+                    wave_sync();
+                    const uint4 P = ring[(head + lane) & (kTileRing - 1u)];
+                    wave_sync();
+                    const double x = (double)(int)P.x, y = (double)(int)P.y, z = (double)(int)P.z;
+                    double b[4] = {x, y, z, __builtin_fma(x, x, __builtin_fma(y, y, z * z))};
+                    if (lane >= nb) b[3] = 1.0e30;
+                    swap_rows32(b[0], b[2]);
+                    swap_rows32(b[1], b[3]);
+                    swap_rows16(b[0], b[1]);
+                    swap_rows16(b[2], b[3]);
+                    uint32_t id[4] = {P.w, 0, P.w, 0};
+                    swap_rows32(id[0], id[2]);
+                    id[1] = id[0];
+                    id[3] = id[2];
+                    swap_rows16(id[0], id[1]);
+                    swap_rows16(id[2], id[3]);
+                    dbl4 D[4];
+                    uint64_t H[16];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) D[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, b[j], C, 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            H[4 * j + i] = __ballot(D[j][i] <= thr[i]);
+                            if (EXCL) H[4 * j + i] &= __ballot(id[j] != selfp[i]);
+                        }
+                    if (!STASH) {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) cnt[j & 3] = add_bit(cnt[j & 3], H[j]);
+                    } else {
+                        // every lane writes its own hits, from its place in the
+                        // prefix of their numbers (past the buffer: counted only)
+                        uint32_t mc = 0;
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) mc = add_bit(mc, H[j]);
+                        const uint32_t incl = scan_add(mc);
+                        const uint32_t n = lane_val(incl, 63);
+                        uint64_t* w = hb + (hcount + incl - mc);
+                        if (hcount + n <= kTileHits) {
+#pragma unroll
+                            for (int j = 0; j < 16; ++j)
+                                if (__builtin_expect(lane_in(H[j]), 1)) {
+                                    *w = ((uint64_t)__double_as_longlong(D[j >> 2][j & 3]) << sh) | id[j >> 2];
+                                    ++w;
+                                }
+                        }
+                        hcount += n;
+                    }
+                    head = (head + 64u) & (kTileRing - 1u);
+                };
+                asm volatile("" : "+v"(lane));
+                // ---- rows of cells within reach of the box, in chunks
+                const int ax[3] = {(int)o[0], (int)o[1], (int)o[2]};
+                int Y0 = (ax[1] + lo[1] - R) >> F, Y1 = (ax[1] + hi[1] + R) >> F;
+                int Z0 = (ax[2] + lo[2] - R) >> F, Z1 = (ax[2] + hi[2] + R) >> F;
+                if (!(L.cyc & 2u)) {
+                    Y0 = max(Y0, 0);
+                    Y1 = min(Y1, (1 << L.lg[1]) - 1);
+                }
+                if (!(L.cyc & 4u)) {
+                    Z0 = max(Z0, 0);
+                    Z1 = min(Z1, (1 << L.lg[2]) - 1);
+                }
+                const uint32_t ny = (uint32_t)(Y1 - Y0 + 1), nz = (uint32_t)(Z1 - Z0 + 1);
+                const uint32_t NR = ny * nz + (outside ? 1u : 0u);
+                const float inv_ny = 1.0f / (float)ny;
+                for (uint32_t rb = 0; rb < NR; rb += kTileRows) {
+                    const uint32_t clen = min(kTileRows, NR - rb);
+                    uint32_t rex[kTileLayers], rin[kTileLayers];
+                    uint32_t carry = 0;
+#pragma unroll
+                    for (uint32_t k = 0; k < kTileLayers; ++k) {
+                        rex[k] = rin[k] = 0u;
+                        if (k * 64u < clen) {
+                            const uint32_t e = rb + k * 64u + lane;
+                            const bool act = k * 64u + lane < clen;
+                            const bool is_out = outside && e + 1u == NR;
+                            bool live = act && !is_out;
+                            const uint32_t iz = (uint32_t)(((float)e + 0.5f) * inv_ny);
+                            const int ty = Y0 + (int)(e - iz * ny), tz = Z0 + (int)iz;
+                            const int ylo = ty << F, zlo = tz << F;
+                            const int gy = max(0, max(ylo - (ax[1] + hi[1]), ax[1] + lo[1] - ylo - (int)E1));
+                            const int gz = max(0, max(zlo - (ax[2] + hi[2]), ax[2] + lo[2] - zlo - (int)E1));
+                            const float g2 = (float)gy * (float)gy + (float)gz * (float)gz;
+                            live = live && g2 <= R2f;
+                            const int X = live ? (int)__builtin_amdgcn_sqrtf(R2f - g2) + 2 : 0;
+                            uint32_t uy = (uint32_t)ty, uz = (uint32_t)tz;
+                            if (L.cyc & 2u) uy &= (1u << L.lg[1]) - 1u;
+                            if (L.cyc & 4u) uz &= (1u << L.lg[2]) - 1u;
+                            if (!live) uy = uz = 0u;
+                            const int xl = ax[0] + lo[0] - X, xh = ax[0] + hi[0] + X;
+                            RowRef r = row_ranges(L, pack_cell(L, 0u, uy, uz), xl >> F, xh >> F, 1, 0, live);
+                            if (L.xsorted && r.plain && r.cnt1 >= kNarrowMin && *L.xsorted)
+                                narrow_x(L, r, (uint32_t)max(xl, 0), (uint32_t)xh);
+                            if (is_out && act) {
+                                r.st0 = L.cs[L.ncells];
+                                r.cnt0 = L.cs[L.ncells + 1] - r.st0;
+                                r.cnt1 = 0u;
+                            }
+                            const uint32_t tl = act ? r.cnt0 + r.cnt1 : 0u;
+                            const uint32_t ci = scan_add(tl);
+                            const uint32_t ce = carry + ci - tl;
+                            if (act) {
+                                rpos[k * 64u + lane] = make_uint2(r.st0 - ce, r.st1 - (ce + r.cnt0));
+                                rbnd[k * 64u + lane] = ce + r.cnt0;
+                            }
+                            rex[k] = ce;
+                            rin[k] = ce + tl;
+                            carry += lane_val(ci, 63);
+                        }
+                    }
+                    const uint32_t CT = carry;
+                    // owner row of each candidate slot, as in group_count_kernel
+                    uint8_t* own8 = (uint8_t*)own;
+                    uint32_t wcarry = 0;
+                    auto locate = [&](uint32_t cb) -> uint32_t {
+                        const uint32_t w0 = cb & ~255u, wo = cb - w0;
+                        if (wo == 0) {
+                            wave_sync();
+                            own[lane] = 0;
+                            wave_sync();
+#pragma unroll
+                            for (uint32_t k = 0; k < kTileLayers; ++k)
+                                if (rin[k] > rex[k] && rex[k] < w0 + 256u && rin[k] > w0)
+                                    own8[rex[k] > w0 ? rex[k] - w0 : 0] = (uint8_t)(k * 64u + lane + 1u);
+                            wave_sync();
+                            wcarry = 0;
+                        }
+                        const uint32_t m = max(scan_max((uint32_t)own8[wo + lane]), wcarry);
+                        wcarry = lane_val(m, 63);
+                        const uint32_t o1 = max(m, 1u) - 1u;
+                        const uint2 rp = rpos[o1];
+                        const uint32_t g = cb + lane;
+                        // (record 0 past the end)
+                        return g < CT ? (g < rbnd[o1] ? rp.x : rp.y) + g : 0u;
+                    };
+                    if (CT > 0) {
+                        // the next step's records load while this step's are
+                        // staged (lanes past the end load record 0)
+                        uint4 P = L.pts[locate(0)];
+                        for (uint32_t cb = 0; cb < CT; cb += 64) {
+                            const uint4 P1 = L.pts[locate(cb + 64)];
+                            // candidates within reach of the box into the ring
+                            const uint32_t pv[3] = {P.x, P.y, P.z};
+                            int p3[3];
+                            float g2 = 0.0f;
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) {
+                                p3[a] = (int)(((pv[a] - o[a]) + aw.half[a]) & aw.mask[a]) - (int)aw.half[a];
+                                const float g = (float)(p3[a] - min(max(p3[a], lo[a]), hi[a]));
+                                g2 = __builtin_fmaf(g, g, g2);
+                            }
+                            uint64_t M = __ballot(g2 <= R2f);
+                            if (CT - cb < 64u) M &= (1ull << (CT - cb)) - 1ull;
+                            const uint32_t at = lanes_below(M, head + fill) & (kTileRing - 1u);
+                            if (lane_in(M)) ring[at] = make_uint4((uint32_t)p3[0], (uint32_t)p3[1], (uint32_t)p3[2], P.w);
+                            fill += (uint32_t)__popcll(M);
+                            if (fill >= 64u) {
+                                batch(64u);
+                                fill -= 64u;
+                            }
+                            P = P1;
+                        }
+                    }
+                    wave_sync();
+                }
+                if (fill > 0) batch(fill);
+                uint32_t nq = 0;
+                if (!STASH) {
+                    // slot s = quad' + 4 i was counted by the lanes of quad'
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t v = bperm(row_sum(cnt[i]), (slot & 3u) << 4);
+                        nq = (slot >> 2) == (uint32_t)i ? v : nq;
+                    }
+                    if (mine && lane < kTileQ) A.row_ptr[row] = (int64_t)nq;
+                    r0 += ng;
+                    if (r0 < rend) Q = group();
+                    continue;
+                }
+                const uint32_t total = hcount;
+                if (total > kTileHits && ng > 1u) {
+                    // too many hits: the group again with as many queries as are
+                    // expected to fit
+                    nlim = max(1u, min(ng - 1u, (uint32_t)((uint64_t)ng * (kTileHits - kTileHits / 8u) / total)));
+                    Q = group();
+                    continue;
+                }
+                const bool fits = total <= kTileHits;
+                if (nlim < kTileQ && total + total / ng + kTileHits / 16u <= kTileHits) ++nlim;
+                const uint32_t n0 = ng;  // (the group's queries)
+                r0 += ng;
+                // the next group's queries load during the sort
+                uint4 Qn = make_uint4(0, 0, 0, 0);
+                if (r0 < rend) Qn = group();
+                // ---- sort (in registers and in place): bucket counts, which
+                // also give the slots' hits
+                asm volatile("" : "+v"(lane));
+                constexpr uint32_t kTileSteps = kTileHits / 64;
+                uint64_t key[kTileSteps];
+                uint32_t bs[kTileSteps];  // bucket | place in bucket << 16
+                uint32_t qs0 = 0, near = 0;  // near: keys of the fullest bucket
+                if (fits) {
+                    uint4* h4 = (uint4*)hh;
+                    for (uint32_t t = lane; t < kTileQ * kTileBuckets / 4; t += 64) h4[t] = make_uint4(0, 0, 0, 0);
+                    wave_sync();
+#pragma unroll
+                    for (uint32_t k0 = 0; k0 < kTileSteps; k0 += 4) {
+                        // (lanes past the end count into a spare bucket)
+                        if (k0 * 64u < total) {
+#pragma unroll
+                            for (uint32_t k = k0; k < k0 + 4 && k < kTileSteps; ++k) key[k] = hb[k * 64u + lane];
+#pragma unroll
+                            for (uint32_t k = k0; k < k0 + 4 && k < kTileSteps; ++k) {
+                                const uint32_t kh = (uint32_t)(key[k] >> 32);
+                                const float v = (float)((kh >> 4) & 0xFFFFFFu);
+                                const uint32_t b =
+                                    ((kh >> 28) * kTileBuckets) + min((uint32_t)(v * scale), kTileBuckets - 1u);
+                                bs[k] = k * 64u + lane < total ? b : kTileQ * kTileBuckets;
+                            }
+#pragma unroll
+                            for (uint32_t k = k0; k < k0 + 4 && k < kTileSteps; ++k)
+                                bs[k] |= atomicAdd(&hh[bs[k]], 1u) << 16;
+                        }
+                    }
+                    wave_sync();
+                    constexpr int kPer = kTileQ * kTileBuckets / 64;
+                    uint32_t v[kPer], sum = 0, most = 0;
+#pragma unroll
+                    for (int k = 0; k < kPer / 4; ++k) {
+                        const uint4 w = h4[lane * (kPer / 4) + k];
+                        v[4 * k] = w.x;
+                        v[4 * k + 1] = w.y;
+                        v[4 * k + 2] = w.z;
+                        v[4 * k + 3] = w.w;
+                        sum += w.x + w.y + w.z + w.w;
+                        most = max(max(most, max(w.x, w.y)), max(w.z, w.w));
+                    }
+                    near = lane_val(scan_max(most), 63);
+                    uint32_t run = scan_add(sum) - sum;
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k) {
+                        const uint32_t n = v[k];
+                        v[k] = run;
+                        run += n;
+                    }
+#pragma unroll
+                    for (int k = 0; k < kPer / 4; ++k)
+                        h4[lane * (kPer / 4) + k] = make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+                    if (lane == 0) hh[kTileQ * kTileBuckets] = total;
+                    wave_sync();
+                    qs0 = hh[slot * kTileBuckets];
+                    nq = hh[(slot + 1u) * kTileBuckets] - qs0;
+                } else {
+                    // a row longer than the buffer, alone in its group
+                    nq = total;
+                }
+                // ---- row sizes (lanes 0 .. n0 - 1 hold the slots) and room in
+                // the stash
+                const bool write = lane < n0;
+                if (write) A.row_ptr[row] = (int64_t)nq;
+                bool ok = fits;
+                if (ok && total > 0 && cur + total > lim) {
+                    ok = false;
+                    if (!dry) {
+                        const uint32_t grab = max(A.stash_chunk, total);
+                        uint32_t t = 0;
+                        if (lane == 0) t = atomicAdd(A.stash_ctr + region * SPHIDX_QSTRIDE, grab);
+                        t = uni(t);
+                        if ((uint64_t)t + grab <= A.stash_region) {
+                            cur = region * A.stash_region + t;
+                            lim = cur + grab;
+                            ok = true;
+                        } else {
+                            dry = true;
+                        }
+                    }
+                }
+                if (ok && total > 0) {
+                    // keys to their buckets; the keys are all in registers, so
+                    // the buffer is written in place
+#pragma unroll
+                    for (uint32_t k0 = 0; k0 < kTileSteps; k0 += 4) {
+                        if (k0 * 64u < total) {
+                            uint32_t to[4];
+#pragma unroll
+                            for (uint32_t k = k0; k < k0 + 4 && k < kTileSteps; ++k)
+                                to[k - k0] = hh[bs[k] & 0xFFFFu] + (bs[k] >> 16);
+#pragma unroll
+                            for (uint32_t k = k0; k < k0 + 4 && k < kTileSteps; ++k)
+                                hb[k * 64u + lane < total ? to[k - k0] : kTileHits] = key[k];
+                        }
+                    }
+                    asm volatile("" : "+v"(lane));
+                    // (past the last key: nothing smaller)
+                    for (uint32_t t = total + lane; t < kTileHits; t += 64) hb[t] = ~0ull;
+                    wave_sync();
+                    // In bucket order a key is out of place only among its
+                    // bucket's keys: its rank is its place, plus the smaller
+                    // keys after it, less the larger ones before it, none
+                    // further away than the fullest bucket is long.
+                    const uint32_t idm = sh >= 32u ? ~0u : (1u << sh) - 1u;
+                    if (near <= kTileNear + 1u) {
+                        // lane l takes kTileSteps keys in a row: pairs inside a
+                        // lane are compared in registers, those across with the
+                        // first keys of the next lane
+                        uint64_t next[kTileNear];
+                        uint32_t rk[kTileSteps];
+#pragma unroll
+                        for (uint32_t k = 0; k < kTileSteps; ++k) {
+                            key[k] = hb[lane * kTileSteps + k];
+                            rk[k] = lane * kTileSteps + k;
+                        }
+#pragma unroll
+                        for (uint32_t k = 0; k < kTileNear; ++k)
+                            if (k + 1u < near) next[k] = next_lane(key[k]);
+#pragma unroll
+                        for (uint32_t d = 1; d <= kTileNear; ++d) {
+                            if (d >= near) break;
+#pragma unroll
+                            for (uint32_t k = 0; k < kTileSteps; ++k) {
+                                const bool in = k + d < kTileSteps;
+                                const uint64_t m = __ballot((in ? key[k + d] : next[k + d - kTileSteps]) < key[k]);
+                                rk[k] = add_bit(rk[k], m);
+                                if (in)
+                                    rk[k + d] = sub_bit(rk[k + d], m);
+                                else
+                                    rk[k + d - kTileSteps] = sub_bit(rk[k + d - kTileSteps], m << 1);
+                            }
+                        }
+                        wave_sync();
+#pragma unroll
+                        for (uint32_t k = 0; k < kTileSteps; ++k) hb[rk[k]] = key[k];
+                        wave_sync();
+                        for (uint32_t t = lane; t < total; t += 64) {
+                            const uint64_t kv = hb[t];
+                            A.stash_ids[cur + t] = (uint32_t)kv & idm;
+                            if (A.stash_d2) A.stash_d2[cur + t] = (int64_t)((kv << 4) >> (64u - d2b));
+                        }
+                    } else {
+                        for (uint32_t t = lane; t < total; t += 64) {
+                            const uint64_t kv = hb[t];
+                            uint32_t rk = t;
+                            for (uint32_t d = 1; d < near; ++d) {
+                                if (t + d < total && hb[t + d] < kv) ++rk;
+                                if (d <= t && hb[t - d] > kv) --rk;
+                            }
+                            A.stash_ids[cur + rk] = (uint32_t)kv & idm;
+                            if (A.stash_d2) A.stash_d2[cur + rk] = (int64_t)((kv << 4) >> (64u - d2b));
+                        }
+                    }
+                    if (write) A.soff[row] = cur + qs0;
+                    cur += total;
+                } else {
+                    // not kept: the write pass walks these rows again
+                    const bool walk_again = write && nq > 0;
+                    if (write) A.soff[row] = walk_again ? kMaxId : 0u;
+                    const uint64_t wm = __ballot(walk_again);
+                    uint32_t wb0 = 0;
+                    if (wm != 0 && lane == 0) wb0 = atomicAdd(A.walk_count, (uint32_t)__popcll(wm));
+                    wb0 = uni(wb0);
+                    if (walk_again) A.walkq[wb0 + lanes_below(wm)] = qpos;
+                }
+                wave_sync();
+                Q = Qn;
+            }
+        }
+    });
+}
+
+// ---------------------------------------------------------------------------
 // Pass 1, radius rows that fit the LDS buffer: collect, sort, store.
 
 template <int METHOD, bool TLDS, bool FROM_LIST>
@@ -2052,13 +2777,14 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
     // after a stashing count pass only the rows it did not keep are walked:
     // the main launch takes the walk list, the list launch skips kept rows
     const bool stashed = A.stash_hdr[kHdrMode] != 0u;
-    const bool from_walk = !FROM_LIST && stashed;
+    const bool from_walk = !FROM_LIST && stashed, tiled = A.stash_hdr[kHdrTiles] != 0u;
     const uint32_t idbits = L.n > 1 ? 32u - (uint32_t)__builtin_clz(L.n - 1u) : 0u;  // ids are below n
     const uint32_t nq = FROM_LIST ? uni(*A.list_count) : (from_walk ? uni(*A.walk_count) : A.Q);
     for_each_query(nq, A, queue_set(A, FROM_LIST ? (int)A.list_set : (from_walk ? kQWalk : kQWrite)),
                    [&](uint32_t ti_) {
         const uint32_t qi = FROM_LIST ? uni(A.list[ti_]) : (from_walk ? uni(A.walkq[ti_]) : ti_);
-        const Query s = load_query(L, A, qi);
+        const bool bare = METHOD == kSphere && from_walk && tiled && qi < L.cs[L.ncells];
+        const Query s = bare ? tile_query(L, T, A, qi) : load_query(L, A, qi);
         if (FROM_LIST && stashed && uni(A.soff[s.row]) != kMaxId) return;  // copied by the gather kernel
         if ((METHOD == kSphere || METHOD == kPaper) && (s.flags & F_VALID) && !(s.flags & F_SPHERE))
             return;  // fallback list
@@ -2066,8 +2792,17 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
         const uint32_t rowlen = (uint32_t)(A.row_ptr[s.row + 1] - rb);
         if (rowlen == 0 || !(s.flags & F_VALID)) return;
         if ((s.flags & F_KNN) || rowlen > cap) {
-            // handled by the top-M kernel
-            if (lane == 0) A.longq[atomicAdd(A.long_count, 1u)] = qi;
+            // handled by the block and top-M kernels
+            if (lane == 0) {
+                if (bare) {
+                    uint4* d = A.desc + 4 * (size_t)qi;
+                    d[0] = make_uint4(s.q[0], s.q[1], s.q[2], s.row);
+                    d[1] = make_uint4(s.r, 0u, s.flags, s.tb);
+                    d[2] = make_uint4(s.tend, 0u, 0u, 0u);
+                    d[3] = make_uint4(0u, 0u, 0u, 0u);
+                }
+                A.longq[atomicAdd(A.long_count, 1u)] = qi;
+            }
             return;
         }
         uint32_t n = 0, cand = 0, walked = 0;
@@ -2528,11 +3263,12 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
 }
 
 // Zero counter words [begin, end); the count pass also writes the stash
-// header (hdr != NULL: four words) after clearing.
+// header (hdr != NULL: five words) after clearing.
 // Counters sit SPHIDX_QSTRIDE words apart and only those words are read:
 // the others are left as they are.  One block; the stash header, inside the
 // cleared range, is written after every clear.
-__global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv) {
+__global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv,
+                                      uint32_t tiles) {
     for (uint32_t i = begin + threadIdx.x * SPHIDX_QSTRIDE; i < end; i += blockDim.x * SPHIDX_QSTRIDE) c[i] = 0u;
     __syncthreads();
     if (hdr && threadIdx.x == 0) {
@@ -2540,6 +3276,7 @@ __global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end,
         hdr[kHdrElems] = hv.y;
         hdr[kHdrHasD2] = hv.z;
         hdr[kHdrD2Off] = hv.w;
+        hdr[kHdrTiles] = tiles;
     }
 }
 
@@ -2667,6 +3404,70 @@ CopyShape copy_shape(uint32_t Q) {
     return c;
 }
 
+// Wavefronts (blocks) of the tile kernel that the chip holds.
+uint32_t tile_blocks() { return (uint32_t)device_cu_count() * std::min(12u, 160u * 1024u / kTileLds); }
+
+// Whether the count pass takes the tile kernel, and its strips and chunks:
+// all-agents queries of one radius on the sphere tables, in groups, whose keys
+// fit.  The line lies at rows of 12 to 160 expected pairs, and again from nine
+// tenths of the grouped kernel's buffer (sort_cap) up to the length from which
+// one block counts a row: count + write in ms, grouped against tiles, cyclic
+// 64^3 and 128^3: 2 pairs 0.311 / 0.310 (1 M queries) but 0.076 / 0.080 (33 K,
+// one launch more); 12 pairs 0.423 / 0.369; 33 pairs 0.691 / 0.522; 57 pairs
+// 0.203 / 0.177; 134 pairs 2.11 / 1.76; 179 pairs 0.457 / 0.507; 226 pairs
+// 1.88 / 2.11 (groups of four queries waste the matrix rows); 250 pairs
+// 7.41 / 2.48 and 289 pairs 1.33 / 0.40 (the grouped kernel leaves rows past
+// its buffer to the write pass); 349 pairs 2.21 / 2.70.
+bool tile_plan(const LatArgs& L, const TabArgs& T, const QArgs& q, TileArgs& TA) {
+    if (!q.group || q.qx || q.rad || q.mode != SPHIDX_MODE_RADIUS || q.stats || q.select || q.method_out || !T.has ||
+        T.paper || q.Q < 1024u)
+        return false;
+    const uint32_t rm = q.rad_u;
+    if (rm > T.rmax) return false;
+    auto bits = [](uint64_t v) { return v ? 64u - (uint32_t)__builtin_clzll(v) : 0u; };
+    TA.d2bits = std::max(1u, bits((uint64_t)rm * rm));
+    if (4u + TA.d2bits + bits(L.n > 1 ? L.n - 1u : 0u) > 64u) return false;
+    const uint64_t E = 1ull << L.F, reach = (rm + E - 1) >> L.F;
+    const double load = (double)L.n / (double)L.ncells, rc = (double)rm / (double)E;
+    const double hits = load * 4.18879 * rc * rc * rc;
+    if (hits < 12.0 || hits > 320.0 || (hits > 160.0 && hits < 0.9 * q.sort_cap)) return false;
+    // strips about as wide as the side of the cube that holds a group
+    const double side = std::cbrt((double)kTileQ / load);
+    TA.wy = side >= 2.5 ? 2u : side >= 1.4 ? 1u : 0u;
+    TA.wz = side >= 3.5 ? 2u : side >= 1.7 ? 1u : 0u;
+    TA.cl = 31u - (uint32_t)__builtin_clz(kTileCells) - TA.wy - TA.wz;
+    uint32_t* w[3] = {&TA.cl, &TA.wy, &TA.wz};
+    for (int a = 0; a < 3; ++a) {
+        *w[a] = std::min(*w[a], L.lg[a]);
+        // no candidate row or run repeats a cell, no difference leaves its
+        // image, and offsets stay below 2^23
+        auto ok = [&]() {
+            const uint64_t c = 1ull << *w[a];
+            if (((c + reach + 2) << L.F) > (1ull << 23)) return false;
+            return !((L.cyc >> a) & 1u) || 2 * (c + reach + 1) <= (1ull << L.lg[a]);
+        };
+        while (*w[a] > 0 && !ok()) --*w[a];
+        if (!ok()) return false;
+    }
+    TA.nchunks = L.ncells >> (TA.cl + TA.wy + TA.wz);
+    TA.part = std::min(256u, std::max(kTileQ, q.Q / (tile_blocks() * 4u) / kTileQ * kTileQ));
+    return TA.nchunks <= (1u << 22);
+}
+
+hipError_t launch_tiles(const LatArgs& L, const QArgs& q, const TileArgs& TA, hipStream_t st) {
+    tile_items_kernel<<<(TA.nchunks + 255) / 256, 256, 0, st>>>(L, q, TA, q.longq, q.item_count);
+    LatArgs l = L;
+    QArgs a = q;
+    a.tile = 1;  // work items per queue grab
+    TileArgs ta = TA;
+    void* args[] = {&l, &a, &ta};
+    const bool excl = (q.flags & SPHIDX_EXCLUDE_SELF) != 0;
+    return hipLaunchKernel(
+        q.stash ? (excl ? (const void*)tile_count_kernel<true, true> : (const void*)tile_count_kernel<true, false>)
+                : (excl ? (const void*)tile_count_kernel<false, true> : (const void*)tile_count_kernel<false, false>),
+        dim3(tile_blocks()), dim3(64), args, kTileLds, st);
+}
+
 hipError_t launch_copy(const QArgs& q, const LatArgs& L, hipStream_t st) {
     const CopyShape c = copy_shape(q.Q);
     const uint64_t waves = (((uint64_t)q.Q + c.rows - 1) / c.rows) * c.splits;
@@ -2725,9 +3526,15 @@ size_t query_lds_bytes(int pass, uint32_t cap, uint32_t waves, size_t table_byte
     return table_bytes + per * waves;
 }
 
-hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const QArgs& q,
+hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const QArgs& q_in,
                              uint32_t waves_per_block, uint32_t blocks_per_cu, hipStream_t st,
                              hipEvent_t ev_begin, hipEvent_t ev_end) {
+    QArgs q = q_in;
+    TileArgs TA;
+    const bool tiles = pass == 0 && tile_plan(L, T, q, TA);
+    // rows kept by the tile kernel need no descriptor (without the stash the
+    // write pass walks every row)
+    q.tiles = tiles && q.stash ? 1u : 0u;
     // optional timing events around the pass's main kernel(s)
     auto mark = [st](hipEvent_t ev) { return ev ? hipEventRecord(ev, st) : hipSuccess; };
     const size_t tb = tab_lds_bytes(T);
@@ -2768,19 +3575,25 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
         // everything, then the stash header for the write pass
         const uint4 hv = make_uint4(q.stash, q.stash ? q.stash_region * SPHIDX_NREGION : 0u, q.stash_d2 ? 1u : 0u,
                                     q.stash_d2 ? (uint32_t)(((char*)q.stash_d2 - q.stash_base) / 256) : 0u);
-        clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, 0u, SPHIDX_COUNTER_WORDS, q.stash_hdr, hv);
+        clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, 0u, SPHIDX_COUNTER_WORDS, q.stash_hdr, hv, q.tiles);
     } else {
         // the write-side queue sets and the long-row list; the descriptors,
         // the fallback and walk lists, the stash header and the stash
         // counters stay as the count pass left them
         clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, set_words, lists + SPHIDX_QSTRIDE, nullptr,
-                                                 make_uint4(0, 0, 0, 0));
+                                                 make_uint4(0, 0, 0, 0), 0u);
     }
     e = hipGetLastError();
     if (e != hipSuccess || q.Q == 0) return e;
     if (pass == 0) {
-        // per-query descriptors (and, for the sphere method, the fallback list)
-        if (variant == 0)
+        // per-query descriptors (and, for the sphere method, the fallback list);
+        // with the tile kernel, of the objects outside the region only
+        // (none on cyclic axes)
+        if (q.tiles && L.cyc != 7u)
+            setup_kernel<kSphere><<<std::min((q.Q + 255u) / 256u, 512u), 256, 0, st>>>(L, T, q);
+        else if (q.tiles)
+            ;
+        else if (variant == 0)
             setup_kernel<kCube><<<(q.Q + 255) / 256, 256, 0, st>>>(L, T, q);
         else if (variant == 3)
             setup_kernel<kPaper><<<(q.Q + 255) / 256, 256, 0, st>>>(L, T, q);
@@ -2815,7 +3628,9 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
             // extra list, one query per wavefront
             const size_t gl = query_lds_bytes(q.stash ? 5 : 4, q.sort_cap, w, tb);
             const bool gk = q.mode != SPHIDX_MODE_RADIUS;  // K-NN queries in the batch
-            if (q.stash)
+            if (tiles)
+                e = launch_tiles(L, q, TA, st);
+            else if (q.stash)
                 e = launch_ptr(gk ? (either ? SPHIDX_PICK(group_count_kernel, variant, kEither, , true, false, true)
                                             : SPHIDX_PICK(group_count_kernel, variant, kSphere, , true, false, true))
                                   : (either ? SPHIDX_PICK(group_count_kernel, variant, kEither, , true, false, false)
@@ -2830,7 +3645,7 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
             if (e == hipSuccess) e = mark(ev_end);
             if (e != hipSuccess) return e;
             if (long_rows_possible() && (e = launch_long(true, long_list())) != hipSuccess) return e;
-            if (variant != 0 && !either) {
+            if (variant != 0 && !either && !(q.tiles && L.cyc == 7u)) {
                 QArgs qg = ql;
                 qg.list = q.fbq;
                 qg.list_count = q.fb_count;
@@ -2841,6 +3656,8 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
                                0, qg, w, b, gl0, st, L, T);
                 if (e != hipSuccess) return e;
             }
+            // (the tile kernel leaves no radius query to the extra list)
+            if (tiles && !gk) return hipSuccess;
             ql.list = q.xq;
             ql.list_count = q.xq_count;
             ql.list_set = kQExtra;

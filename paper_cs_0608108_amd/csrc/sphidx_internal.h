@@ -138,6 +138,7 @@ struct QArgs {
     uint32_t* xq;       // grouped count: queries left to the one-query-per-wave kernel
     uint32_t* lq_count;
     uint32_t* lq;       // stash mode: radius rows expected to be long, counted one block per row
+    uint32_t* item_count;  // tile count: its work items (kept in longq, free until later launches)
     uint32_t* soff;     // stash mode: per output row, first stash element of its sorted row
     uint32_t* stash_hdr;  // stash header written by the count pass (see StashHdr)
     uint32_t* stash_ctr;  // NQUEUE per-region allocation counters
@@ -164,19 +165,20 @@ struct QArgs {
     uint32_t knn_rev;   // volume choice: K-NN queries below this take the cube
     uint32_t model;     // volume choice: 0 = cells, 1 = estimated lane work
     uint32_t* method_out;  // optional per query row: the walk used
+    uint32_t tiles;        // count pass: the tile kernel counts, so only rows it does not keep get descriptors
     uint32_t long_waves;   // write pass: waves per long radius row (one block each); <= 1: one wave, windowed
 };
 
 // Stash header words (in the counter block): written by the count pass,
 // read by the write pass, which therefore needs no host-side state.
-enum : uint32_t { kHdrMode = 0, kHdrElems = 1, kHdrHasD2 = 2, kHdrD2Off = 3 };
+enum : uint32_t { kHdrMode = 0, kHdrElems = 1, kHdrHasD2 = 2, kHdrD2Off = 3, kHdrTiles = 4 };
 
 #define SPHIDX_NXCD 8           // XCDs of the MI355X: blocks are dispatched to them in turn
 #define SPHIDX_NQUEUE 64        // work queues per set, 8 per XCD: queue q is served by the blocks of XCD q mod 8
 #define SPHIDX_NREGION SPHIDX_NXCD  // stash regions, one per XCD
 #define SPHIDX_QSTRIDE 32       // counters 128 bytes apart: one L2 line each
 #define SPHIDX_NQSETS 7         // count, write, top-M, fallback count, fallback write, walk list, extra list
-#define SPHIDX_NLISTS 6         // long_count, fb_count, walk_count, stash header, xq_count, lq_count
+#define SPHIDX_NLISTS 7         // long_count, fb_count, walk_count, stash header, xq_count, lq_count, item_count
 #define SPHIDX_COUNTER_WORDS \
     ((SPHIDX_NQSETS * SPHIDX_NQUEUE + SPHIDX_NLISTS + SPHIDX_NREGION) * SPHIDX_QSTRIDE)
 #define SPHIDX_MAX_LOG2_SUM 30
