@@ -207,6 +207,28 @@ __device__ __forceinline__ uint32_t pack_cell(const LatArgs& L, uint32_t x, uint
     return (z << (L.lg[0] + L.lg[1])) | (y << L.lg[0]) | x;
 }
 
+// Zero counter words [begin, end), by one block; the count pass also writes the
+// stash header (hdr != NULL: five words), inside the cleared range, after every
+// clear.  Counters sit SPHIDX_QSTRIDE words apart and only those words are
+// read: the others are left as they are.
+__device__ void clear_counters(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv, uint32_t tiles) {
+    for (uint32_t i = begin + threadIdx.x * SPHIDX_QSTRIDE; i < end; i += blockDim.x * SPHIDX_QSTRIDE) c[i] = 0u;
+    if (!hdr) return;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        hdr[kHdrMode] = hv.x;
+        hdr[kHdrElems] = hv.y;
+        hdr[kHdrHasD2] = hv.z;
+        hdr[kHdrD2Off] = hv.w;
+        hdr[kHdrTiles] = tiles;
+    }
+}
+
+__global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv,
+                                      uint32_t tiles) {
+    clear_counters(c, begin, end, hdr, hv, tiles);
+}
+
 // One thread per query: centre, radius, K, method and walk extent.
 // K-NN first search radius in the grouped count: the radius of the ball
 // expected to hold knn_target(K) objects at the density around the home cell.
@@ -225,8 +247,15 @@ __host__ __device__ inline float knn_target(float k) {
 
 // Every query; with the tile kernel, the objects outside the region only (a
 // row that kernel does not keep is set up where it is walked, tile_query).
+// With `counters` (a launch of one block) the block first clears the counters
+// and writes the stash header, as clear_counters_kernel.
 template <int METHOD>
-__global__ __launch_bounds__(256) void setup_kernel(LatArgs L, TabArgs T, QArgs A) {
+__global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs A, uint32_t* counters, uint4 hv) {
+    if (counters) {
+        clear_counters(counters, 0u, SPHIDX_COUNTER_WORDS, A.stash_hdr, hv, A.tiles);
+        __threadfence();
+        __syncthreads();
+    }
     const uint32_t first = A.tiles ? L.cs[L.ncells] : 0u, stride = gridDim.x * blockDim.x;
     for (uint32_t i = first + blockIdx.x * blockDim.x + threadIdx.x; uni(i) < A.Q; i += stride) {
     bool range_bad = false, fallback = false, to_list = false, longrow = false;
@@ -345,13 +374,13 @@ __global__ __launch_bounds__(256) void setup_kernel(LatArgs L, TabArgs T, QArgs 
         }
         fallback = valid && tables && !usable;
         // (chosen per query: the main kernels take every walk themselves)
-        to_list = valid && tables && !sphere && A.select != 1u;
+        to_list = valid && tables && !sphere && A.select != 1u && !A.merged;
         // a radius row of the main kernels expected (at the lattice's mean
         // density) to pass 5/4 of a wavefront's row buffer: with the stash
         // and the block kernel, one block counts, orders and keeps it in a
         // single walk instead of a count walk and a write walk
         // (not with per-query statistics, which that kernel does not keep)
-        if (valid && !knn && !to_list && A.stash && A.long_waves > 1 && !A.stats) {
+        if (valid && !knn && !to_list && !(A.merged && !sphere) && A.stash && A.long_waves > 1 && !A.stats) {
             const float rc = (float)r / (float)e;
             const float expect = 4.18879f * rc * rc * rc * ((float)L.n / (float)L.ncells);
             longrow = expect > 1.25f * (float)A.sort_cap;
@@ -2783,7 +2812,7 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
     for_each_query(nq, A, queue_set(A, FROM_LIST ? (int)A.list_set : (from_walk ? kQWalk : kQWrite)),
                    [&](uint32_t ti_) {
         const uint32_t qi = FROM_LIST ? uni(A.list[ti_]) : (from_walk ? uni(A.walkq[ti_]) : ti_);
-        const bool bare = METHOD == kSphere && from_walk && tiled && qi < L.cs[L.ncells];
+        const bool bare = (METHOD == kSphere || METHOD == kEither) && from_walk && tiled && qi < L.cs[L.ncells];
         const Query s = bare ? tile_query(L, T, A, qi) : load_query(L, A, qi);
         if (FROM_LIST && stashed && uni(A.soff[s.row]) != kMaxId) return;  // copied by the gather kernel
         if ((METHOD == kSphere || METHOD == kPaper) && (s.flags & F_VALID) && !(s.flags & F_SPHERE))
@@ -3262,24 +3291,6 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
     }
 }
 
-// Zero counter words [begin, end); the count pass also writes the stash
-// header (hdr != NULL: five words) after clearing.
-// Counters sit SPHIDX_QSTRIDE words apart and only those words are read:
-// the others are left as they are.  One block; the stash header, inside the
-// cleared range, is written after every clear.
-__global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv,
-                                      uint32_t tiles) {
-    for (uint32_t i = begin + threadIdx.x * SPHIDX_QSTRIDE; i < end; i += blockDim.x * SPHIDX_QSTRIDE) c[i] = 0u;
-    __syncthreads();
-    if (hdr && threadIdx.x == 0) {
-        hdr[kHdrMode] = hv.x;
-        hdr[kHdrElems] = hv.y;
-        hdr[kHdrHasD2] = hv.z;
-        hdr[kHdrD2Off] = hv.w;
-        hdr[kHdrTiles] = tiles;
-    }
-}
-
 // Pass 1 with the stash: copy each kept row into place.  A wavefront takes
 // `rows` (at most 64) consecutive output rows and reads each one's stash offset
 // (kept per output row) and its place from row_ptr.  Their objects are numbered
@@ -3297,9 +3308,16 @@ __global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end,
 // again instead, and the walk list takes query slots: then the wavefront takes
 // consecutive query slots and finds each one's output row (a group's first
 // wavefront lists them, the others have nothing to do).
+// First of the write pass, its first block also clears that pass's counters:
+// the write-side queue sets and the long-row list; the descriptors, the
+// fallback and walk lists, the stash header and the stash counters stay as the
+// count pass left them.
 __global__ __launch_bounds__(256) void gather_kernel(QArgs A, const uint4* pts, uint32_t* status, uint32_t rows,
                                                      uint32_t splits) {
     __shared__ uint32_t starts_all[4 * 64];
+    if (blockIdx.x == 0)
+        clear_counters(A.queues, SPHIDX_NQUEUE * SPHIDX_QSTRIDE, (SPHIDX_NQSETS * SPHIDX_NQUEUE + 1u) * SPHIDX_QSTRIDE,
+                       nullptr, make_uint4(0, 0, 0, 0), 0u);
     const uint32_t* hdr = A.stash_hdr;
     if (hdr[kHdrMode] == 0u) return;
     if (A.row_ptr[A.Q] > A.capacity) {
@@ -3484,11 +3502,21 @@ hipError_t launch_copy(const QArgs& q, const LatArgs& L, hipStream_t st) {
 #define SPHIDX_PICKP(KERNEL, variant, SPH, ...) \
     ((variant) == 3 ? (const void*)KERNEL<kPaper, false __VA_ARGS__> : SPHIDX_PICK(KERNEL, variant, SPH, __VA_ARGS__))
 
+// Small batches, where launches and not work are what a call costs: up to
+// kSmallSetup queries one block clears the counters and sets up every query,
+// and up to kMergedQ the main kernels walk the fallback queries too, instead of
+// a list and a launch of their own in each pass; no launch has many more
+// wavefronts than queries (2,048 empty blocks take 4 us to come and go).
+constexpr uint32_t kSmallSetup = 1024, kMergedQ = 8192;
+
 hipError_t launch_ptr(const void* fn, uint32_t nq, const QArgs& q, uint32_t waves, uint32_t bpc, size_t shmem,
                       hipStream_t st, const LatArgs& L, const TabArgs& T) {
     uint32_t blocks;
     if (q.persistent) {
-        blocks = (uint32_t)device_cu_count() * bpc;
+        // a wavefront for each query of each queue, so that none waits behind
+        // another (list-driven: at most every query; `nq` is 0 there)
+        const uint32_t per = (q.Q + SPHIDX_NQUEUE - 1u) / SPHIDX_NQUEUE;
+        blocks = std::min((uint32_t)device_cu_count() * bpc, SPHIDX_NQUEUE * ((per + waves - 1u) / waves));
     } else {
         const uint64_t per = (uint64_t)waves * q.tile;
         blocks = (uint32_t)((nq + per - 1) / per);
@@ -3535,12 +3563,11 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
     // rows kept by the tile kernel need no descriptor (without the stash the
     // write pass walks every row)
     q.tiles = tiles && q.stash ? 1u : 0u;
+    q.merged = !tiles && T.has && !T.paper && q.select == 0u && q.Q <= kMergedQ ? 1u : 0u;
     // optional timing events around the pass's main kernel(s)
     auto mark = [st](hipEvent_t ev) { return ev ? hipEventRecord(ev, st) : hipSuccess; };
     const size_t tb = tab_lds_bytes(T);
     const int variant = !T.has ? 0 : T.paper ? 3 : (T.lds ? 2 : 1);
-    const uint32_t lists = SPHIDX_NQSETS * SPHIDX_NQUEUE * SPHIDX_QSTRIDE;
-    const uint32_t set_words = SPHIDX_NQUEUE * SPHIDX_QSTRIDE;
     hipError_t e;
     // one block per long radius row (count pass: the rows the setup listed;
     // write pass: rows longer than a wavefront's buffer)
@@ -3558,8 +3585,8 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
         TabArgs t = T;
         QArgs a = qa;
         void* args[] = {&l, &t, &a};
-        return hipLaunchKernel(lf, dim3((uint32_t)device_cu_count() * per_cu), dim3(64u * qa.long_waves), args, lds,
-                               st);
+        return hipLaunchKernel(lf, dim3(std::min((uint32_t)device_cu_count() * per_cu, qa.Q)), dim3(64u * qa.long_waves),
+                               args, lds, st);
     };
     // whether the setup can have listed rows for it: a radius at the tables'
     // cap (per-query radii) or the batch's radius, at the lattice's mean
@@ -3572,40 +3599,33 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
         return 4.18879 * rc * rc * rc * ((double)L.n / (double)L.ncells) > 0.98 * 1.25 * (double)q.sort_cap;
     };
     if (pass == 0) {
-        // everything, then the stash header for the write pass
+        // every counter cleared, the stash header for the write pass, and the
+        // per-query descriptors (for the sphere method, the fallback list too);
+        // with the tile kernel, of the objects outside the region only (none on
+        // cyclic axes)
         const uint4 hv = make_uint4(q.stash, q.stash ? q.stash_region * SPHIDX_NREGION : 0u, q.stash_d2 ? 1u : 0u,
                                     q.stash_d2 ? (uint32_t)(((char*)q.stash_d2 - q.stash_base) / 256) : 0u);
-        clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, 0u, SPHIDX_COUNTER_WORDS, q.stash_hdr, hv, q.tiles);
-    } else {
-        // the write-side queue sets and the long-row list; the descriptors,
-        // the fallback and walk lists, the stash header and the stash
-        // counters stay as the count pass left them
-        clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, set_words, lists + SPHIDX_QSTRIDE, nullptr,
-                                                 make_uint4(0, 0, 0, 0), 0u);
+        const bool setup = q.Q > 0 && !(q.tiles && L.cyc == 7u), one = setup && q.Q <= kSmallSetup;
+        if (!one) clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, 0u, SPHIDX_COUNTER_WORDS, q.stash_hdr, hv, q.tiles);
+        if (setup) {
+            const uint32_t threads = one ? std::max(256u, (q.Q + 63u) & ~63u) : 256u;
+            const uint32_t blocks = one ? 1u : q.tiles ? std::min((q.Q + 255u) / 256u, 512u) : (q.Q + 255u) / 256u;
+            uint32_t* counters = one ? q.queues : nullptr;
+            if (variant == 0)
+                setup_kernel<kCube><<<blocks, threads, 0, st>>>(L, T, q, counters, hv);
+            else if (variant == 3)
+                setup_kernel<kPaper><<<blocks, threads, 0, st>>>(L, T, q, counters, hv);
+            else
+                setup_kernel<kSphere><<<blocks, threads, 0, st>>>(L, T, q, counters, hv);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    e = hipGetLastError();
-    if (e != hipSuccess || q.Q == 0) return e;
-    if (pass == 0) {
-        // per-query descriptors (and, for the sphere method, the fallback list);
-        // with the tile kernel, of the objects outside the region only
-        // (none on cyclic axes)
-        if (q.tiles && L.cyc != 7u)
-            setup_kernel<kSphere><<<std::min((q.Q + 255u) / 256u, 512u), 256, 0, st>>>(L, T, q);
-        else if (q.tiles)
-            ;
-        else if (variant == 0)
-            setup_kernel<kCube><<<(q.Q + 255) / 256, 256, 0, st>>>(L, T, q);
-        else if (variant == 3)
-            setup_kernel<kPaper><<<(q.Q + 255) / 256, 256, 0, st>>>(L, T, q);
-        else
-            setup_kernel<kSphere><<<(q.Q + 255) / 256, 256, 0, st>>>(L, T, q);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    if (q.Q == 0) return hipSuccess;
     const uint32_t w = waves_per_block, b = blocks_per_cu;
     // per-query choice: the main kernels walk the sphere, the cube or the
-    // cell list per query (grouping them apart would split the groups)
-    const bool either = variant != 0 && q.select == 1u;
+    // cell list per query (grouping them apart would split the groups); small
+    // batches take their fallback queries in the same way
+    const bool either = q.merged || (variant != 0 && q.select == 1u);
     QArgs ql = q;  // list-driven launches: persistent, grabs sized from the list
     ql.persistent = 1;
     // the count pass's long rows: the setup's list, with the walk-list queue

@@ -166,6 +166,7 @@ struct QArgs {
     uint32_t model;     // volume choice: 0 = cells, 1 = estimated lane work
     uint32_t* method_out;  // optional per query row: the walk used
     uint32_t tiles;        // count pass: the tile kernel counts, so only rows it does not keep get descriptors
+    uint32_t merged;       // the main kernels take the fallback queries themselves (small batches)
     uint32_t long_waves;   // write pass: waves per long radius row (one block each); <= 1: one wave, windowed
 };
 
