@@ -329,7 +329,10 @@ typedef struct {
                             keeping the first K when it holds K (rows short of K are searched
                             again in groups at a larger radius, then one query per
                             wavefront; the stash needs K pairs per such row);
-                            0: one query per wavefront */
+                            0: the library's choice: groups for all-agents batches of the
+                            sphere method from 16,384 queries on whose expected rows fit
+                            the buffer (K-NN: K <= 64 and rows kept), else one query per
+                            wavefront (always with per-query statistics) */
     /* METHOD_AUTO (Appendix: weighting factor and reversal distances).  A radius query takes
      * the sphere when select_weight/256 * (sphere cells) <= (cube cells), else the cube; then
      * the non-empty list instead if it holds fewer cells than the one chosen (plain counts).

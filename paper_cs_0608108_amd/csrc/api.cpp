@@ -295,6 +295,27 @@ void plan_stash(QArgs& A, const sphidx_csr* csr, const Launch& ln, bool interior
     A.stash_chunk = (uint32_t)std::min<uint64_t>(8192, std::max<uint64_t>(ln.cap, region / (per * 8)));
 }
 
+// Whether the count pass takes a batch in groups when the launch leaves it to
+// the library (grouped = 0): all-agents batches, whose neighbouring queries
+// share rows and candidates, of 16,384 queries and more (below, one launch
+// more costs what the groups save), with rows that fit the hit buffer; K-NN
+// only when its rows are kept, as a row short of K is searched again.  Count +
+// write in ms, one query per wavefront against groups (or tiles), cyclic and
+// clipped lattices: r = 2.5 cells at 0.5 objects per cell, 16 K queries 0.100 /
+// 0.082; r = 3, 131 K 0.230 / 0.166; r = 4 (135 pairs) 0.342 / 0.331, 227 pairs
+// 1.87 / 1.97; uneven radii to 4 cells, 1 M 1.22 / 0.79; K = 10, 99 K 0.321 /
+// 0.260; K = 40 0.462 / 0.434; K = 16 in clusters, 262 K 0.718 / 0.288; without
+// the stash r = 3 0.309 / 0.261 but K = 10 0.366 / 0.524.  (Given centres are
+// left alone: a service's mixed batch took 1.39 / 1.56.)
+bool choose_groups(const sphidx_lattice* lat, const sphidx_tables* tab, const QArgs& A, const Launch& ln) {
+    if (ln.method != SPHIDX_METHOD_SPHERE || A.qx || A.Q < 16384u || A.stats || lat->ncells == 0) return false;
+    if (A.mode != SPHIDX_MODE_RADIUS && (!A.stash || (!A.kk && A.k_u > 64u))) return false;
+    if (A.mode == SPHIDX_MODE_KNN) return true;
+    const double r = (double)(A.rad ? tab->rmax_fx : A.rad_u) / (double)(1u << lat->desc.frac_bits);
+    const double hits = 4.18879 * r * r * r * (double)lat->n / (double)lat->ncells;
+    return hits <= (A.rad ? 0.75 : 0.625) * A.sort_cap;
+}
+
 void* scan_tmp_of(sphidx_csr* csr, uint32_t Q) { return (char*)csr->workspace_dev + query_layout(Q).scan; }
 
 sphidx_status dev_err(hipError_t e) { return e == hipSuccess ? SPHIDX_OK : SPHIDX_ERR_DEVICE; }
@@ -378,7 +399,8 @@ sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables*
     // persistent schedule; not with per-query statistics or the interior
     // shortcut, which the grouped kernel does not implement)
     // (the paper's cell tables are walked one query per wavefront)
-    A.group = pass == 0 && ln.persistent && ln.grouped && !A.interior && !T.paper;
+    A.group = pass == 0 && ln.persistent && !A.interior && !T.paper &&
+              (ln.grouped || choose_groups(lat, tab, A, ln));
     if (pass == 0) {
         s = dev_err(launch_query_pass(0, L, T, A, ln.waves, ln.bpc, st, ln.ev_begin, ln.ev_end));
         if (s != SPHIDX_OK) return s;

@@ -49,3 +49,27 @@ def test_small_batches_match_oracle(world, q):
             assert_same(run(sx, lat, tab, r, k=5, mode=sx.MODE_KNN, queries=cen, launch=ln, stash=stash), refk, "knn")
     code, flags = lat.status()
     assert code == sx.OK, (code, flags)
+
+
+@pytest.mark.parametrize("n", [16383, 16384, 40001])
+def test_default_launch_of_all_agents_batches(orc, n):
+    """Either side of the size from which the library takes them in groups."""
+    from paper_cs_0608108_amd import sphidx as sx
+    rng = np.random.default_rng(n)
+    log2, F, mask = (5, 5, 5), 12, 3
+    pts = tuple(rng.integers(0, 32 << F, n).astype(np.uint32) for _ in range(3))
+    pts[2][:50] += 32 << F
+    lat = lattice(sx, log2, F, mask, pts)
+    tab = sx.Tables(lat, 2, 4 << F)
+    g = orc.Grid(orc.Lattice(log2, F, mask), pts)
+    r = rng.integers(0, 2 << F, n).astype(np.uint32)
+    cap = np.full(n, 4 << F, np.uint32)
+    k = np.where(rng.random(n) < 0.5, rng.integers(1, 20, n), 0).astype(np.uint32)
+    rm = np.where(k > 0, cap, r).astype(np.uint32)
+    cases = [("radius", 2 << F, None, sx.MODE_RADIUS, g.radius(2 << F)), ("uneven", r, None, sx.MODE_RADIUS, g.radius(r)),
+             ("knn", 4 << F, 10, sx.MODE_KNN, g.mixed(np.full(n, 10, np.uint32), cap)),
+             ("mixed", rm, k, sx.MODE_MIXED, g.mixed(k, rm))]
+    for what, rr, kk, mode, ref in cases:
+        for stash in (False, True):
+            say(f"default launch n {n} {what} stash {stash}")
+            assert_same(run(sx, lat, tab, rr, k=kk, mode=mode, stash=stash), ref, what)
