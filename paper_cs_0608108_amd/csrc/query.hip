@@ -1172,7 +1172,8 @@ __device__ __forceinline__ uint32_t sort_bucket(uint64_t d2, float scale, uint32
 }
 
 __device__ void bucket_sort_store(const uint64_t* td, const uint32_t* ti, uint64_t* sd, uint32_t* si, uint32_t* hist,
-                                  uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2) {
+                                  uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2,
+                                  uint32_t limit = ~0u) {
     const uint32_t lane = lane_id();
     if (n == 0) return;
     const float scale = r2 > 0 ? (float)n / (float)r2 : 0.0f;
@@ -1217,6 +1218,7 @@ __device__ void bucket_sort_store(const uint64_t* td, const uint32_t* ti, uint64
         const uint32_t lo = hist[b], hi = b + 1 < n ? hist[b + 1] : n;
         uint32_t rank = lo;
         for (uint32_t j = lo; j < hi; ++j) rank += key_less(sd[j], si[j], d, id) ? 1u : 0u;
+        if (rank >= limit) continue;
         dst_ids[rank] = id;
         if (dst_d2) dst_d2[rank] = (int64_t)d;
     }
@@ -1346,6 +1348,20 @@ __device__ __forceinline__ uint32_t topm_registers(const LatArgs& L, const TabAr
 // ---------------------------------------------------------------------------
 // Pass 0: row sizes
 
+// A row that the count pass could not keep: on the big list when it is one for
+// the block-per-row and top-M kernels (K-NN rows, radius rows longer than a
+// wavefront's buffer), else on the walk list of the write kernel.  (One lane.
+// A wavefront that only passes such rows on costs as much as one that walks a
+// short row: 10,000 of them on the walk list took the write kernel 127 us.
+// The fallback list's rows stay on the walk list: its write kernel passes on
+// what it does not keep.)
+__device__ __forceinline__ void list_row_again(const QArgs& A, uint32_t qi, bool big) {
+    if (big)
+        A.bigq[atomicAdd(A.big_count, 1u)] = qi;
+    else
+        A.walkq[atomicAdd(A.walk_count, 1u)] = qi;
+}
+
 // Queue sets of the work counters.
 constexpr int kQCount = 0, kQWrite = 1, kQTopm = 2, kQFbCount = 3, kQFbWrite = 4, kQWalk = 5, kQExtra = 6;
 // the count pass's last list (rows the second grouped round left) takes the
@@ -1386,15 +1402,16 @@ __device__ void sort_small_store(const uint64_t* td, const uint32_t* ti, uint64_
     wave_sync();
 }
 
-// Order the n <= cap pairs of one row by (dist^2, id) and store them at dst.
+// Order the n <= cap pairs of one row by (dist^2, id) and store them (the first
+// `limit` of them, at least 64) at dst.
 __device__ __forceinline__ void sort_row_store(const uint64_t* td, const uint32_t* ti, uint64_t* sd, uint32_t* si,
                                                uint32_t* hist, uint32_t n, uint64_t r2, uint32_t idbits,
-                                               uint32_t* dst_ids, int64_t* dst_d2) {
+                                               uint32_t* dst_ids, int64_t* dst_d2, uint32_t limit = ~0u) {
     const uint32_t r2bits = r2 ? 64u - (uint32_t)__builtin_clzll(r2) : 0u;
     if (n <= 64 && r2bits + idbits <= 64)
-        sort_small_store(td, ti, sd, n, idbits, dst_ids, dst_d2);
+        sort_small_store(td, ti, sd, n, idbits, dst_ids, dst_d2);  // (n <= 64: `limit` is more)
     else
-        bucket_sort_store(td, ti, sd, si, hist, n, r2, dst_ids, dst_d2);
+        bucket_sort_store(td, ti, sd, si, hist, n, r2, dst_ids, dst_d2, limit);
 }
 
 // FROM_LIST: a query list (the sphere method's fallback queries, scanned with
@@ -1473,7 +1490,7 @@ __global__ __launch_bounds__(256) void count_kernel(LatArgs L, TabArgs T, QArgs 
                     cur += got;
                 } else {
                     off = kMaxId;
-                    if (lane == 0) A.walkq[atomicAdd(A.walk_count, 1u)] = qi;
+                    if (lane == 0) list_row_again(A, qi, !(FROM_LIST && METHOD == kCube));
                 }
             }
             if (lane == 0) A.soff[s.row] = off;
@@ -1539,7 +1556,7 @@ __global__ __launch_bounds__(256) void count_kernel(LatArgs L, TabArgs T, QArgs 
                     cur += hits;
                 } else {
                     off = kMaxId;
-                    if (lane == 0) A.walkq[atomicAdd(A.walk_count, 1u)] = qi;
+                    if (lane == 0) list_row_again(A, qi, (knn || hits > cap) && !(FROM_LIST && METHOD == kCube));
                 }
             }
             if (lane == 0) A.soff[s.row] = off;
@@ -2077,11 +2094,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                     // not kept: the write pass walks these rows again
                     const bool walk_again = mine && nq > 0;
                     if (mine) A.soff[row] = walk_again ? kMaxId : 0u;
-                    const uint64_t wm = __ballot(walk_again);
-                    uint32_t wb0 = 0;
-                    if (wm != 0 && lane == 0) wb0 = atomicAdd(A.walk_count, (uint32_t)__popcll(wm));
-                    wb0 = uni(wb0);
-                    if (walk_again) A.walkq[wb0 + lanes_below(wm)] = qi;
+                    if (walk_again) list_row_again(A, qi, ((KNN && knn) || nq > A.sort_cap) && !(FROM_LIST && METHOD == kCube));
                 }
             }
             wave_sync();
@@ -2768,11 +2781,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
                     // not kept: the write pass walks these rows again
                     const bool walk_again = write && nq > 0;
                     if (write) A.soff[row] = walk_again ? kMaxId : 0u;
-                    const uint64_t wm = __ballot(walk_again);
-                    uint32_t wb0 = 0;
-                    if (wm != 0 && lane == 0) wb0 = atomicAdd(A.walk_count, (uint32_t)__popcll(wm));
-                    wb0 = uni(wb0);
-                    if (walk_again) A.walkq[wb0 + lanes_below(wm)] = qpos;
+                    // (no descriptor yet: the write kernel makes it and passes a long row on)
+                    if (walk_again) list_row_again(A, qpos, false);
                 }
                 wave_sync();
                 Q = Qn;
@@ -2874,11 +2884,12 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
     char* wb = smem + table_lds_bytes<TLDS>(T) + (size_t)wave * ((size_t)cap * 24 + 64 * 12 + 256);
     uint64_t* tdA = (uint64_t*)wb;
     uint64_t* tdB = tdA + cap;
-    uint64_t* bd = tdB + cap;
-    uint32_t* tiA = (uint32_t*)(bd + 64);
+    uint32_t* tiA = (uint32_t*)(tdB + cap);
     uint32_t* tiB = tiA + cap;
-    uint32_t* bi = tiB + cap;
+    uint64_t* bd = (uint64_t*)(tiB + cap);
+    uint32_t* bi = (uint32_t*)(bd + 64);
     uint32_t* own = bi + 64;
+    uint32_t* hist = (uint32_t*)bd;  // cap <= 256 words over bd, bi and own, between walks
     if (A.row_ptr[A.Q] > A.capacity) {
         if (threadIdx.x == 0) atomicOr(L.status, SPHIDX_FLAG_CAPACITY);
         return;
@@ -2890,9 +2901,14 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
     // list (when this call asks for dist^2 and the stash holds none, the copy
     // placed nothing and every row is searched)
     const bool from_walk = !FROM_LIST && A.stash_hdr[kHdrMode] != 0u && !(A.out_d2 && A.stash_hdr[kHdrHasD2] == 0u);
-    const uint32_t nq = FROM_LIST ? uni(*A.list_count) : from_walk ? uni(*A.walk_count) : A.Q;
+    // (FROM_LIST: the count pass's big list, then the write kernel's long rows)
+    const uint32_t nbig = FROM_LIST || from_walk ? uni(*A.big_count) : 0u;
+    const uint32_t* rest = FROM_LIST ? A.list : A.walkq;
+    const uint32_t nq = FROM_LIST ? nbig + uni(*A.list_count) : from_walk ? nbig + uni(*A.walk_count) : A.Q;
+    const uint32_t idbits = L.n > 1 ? 32u - (uint32_t)__builtin_clz(L.n - 1u) : 0u;  // ids are below n
     for_each_query(nq, A, queue_set(A, kQTopm), [&](uint32_t ti_) {
-        const uint32_t qi = FROM_LIST ? uni(A.list[ti_]) : from_walk ? uni(A.walkq[ti_]) : ti_;
+        const uint32_t qi =
+            ti_ < nbig ? uni(A.bigq[ti_]) : FROM_LIST || from_walk ? uni(rest[ti_ - nbig]) : ti_;
         const Query s = load_query(L, A, qi);
         if (!FROM_LIST && !(s.flags & F_KNN)) return;
         const int64_t rb = A.row_ptr[s.row];
@@ -2908,6 +2924,36 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
         uint64_t ld = 0;
         uint32_t li = 0;
         uint32_t written = 0;
+        if ((s.flags & F_KBOUND) && rowlen > 64u && rowlen <= cap) {
+            // the count pass left a radius that holds K objects, few more of
+            // them: collected whole and sorted once, the first K stored (in
+            // windows when the buffer does not hold them)
+            const uint64_t kb2 = min(s.r2, sq(s.kbr));
+            uint32_t n = 0, cand = 0, walked = 0;
+            walk<METHOD, TLDS, true>(L, T, tab_lds, s, false, walked, [&]() { return kb2; },
+                                     [&](const RowRef& r) -> bool {
+                return for_candidates(L, r.st0, r.cnt0, r.st1, r.cnt1, own, cand,
+                                      [&](bool act, uint32_t p, const uint4& P) -> bool {
+                    const uint64_t d2 = obj_dist2(aw, s, P);
+                    const bool hit = act && d2 <= kb2 && p != s.self;
+                    const uint64_t hm = __ballot(hit);
+                    const uint32_t at = lanes_below(hm, n);
+                    if (hit && at < cap) {
+                        tdA[at] = d2;
+                        tiA[at] = P.w;
+                    }
+                    n += (uint32_t)__popcll(hm);
+                    return n > cap;
+                });
+            });
+            wave_sync();
+            if (n >= rowlen && n <= cap) {
+                sort_row_store(tdA, tiA, tdB, tiB, hist, n, kb2, idbits, A.out_ids + rb,
+                               A.out_d2 ? A.out_d2 + rb : nullptr, rowlen);
+                wave_sync();
+                return;
+            }
+        }
         while (written < rowlen) {
             const uint32_t M = min(cap, rowlen - written);
             const uint32_t target = written + M;
@@ -3044,75 +3090,112 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum) 
     return off + incl - v;
 }
 
-// Sort the block's n <= kLongCap pairs (td, ti) by (dist^2, id) and store
-// them at dst; a pair holds its dist^2 less `base`, at most r2.  The pairs
-// stay where they are: the bucket pass orders their indices (sx), which the
-// rank pass follows.
-__device__ void block_sort_store(const uint64_t* td, const uint32_t* ti, uint32_t* sx, uint32_t* hist,
-                                 uint32_t* wsum, uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2,
-                                 uint64_t base = 0) {
-    const uint32_t tid = threadIdx.x, nt = blockDim.x;
-    const float scale = r2 > 0 ? (float)n / (float)r2 : 0.0f;
+// Order the block's n <= kLongCap keys (dist^2 - base) << idbits | id and store
+// them at dst; the distances are at most span above base.  One counting sort
+// over about n buckets (floor(n v / (v_max + 1)) of v = the top 24 bits of the
+// distance: monotone), the keys held in registers and put in place, then each
+// key's rank from its place and the keys near it (as the tile kernel's).
+// kb[-kNearPad .. n + kNearPad) is the block's.
+constexpr uint32_t kNearPad = 8;
+
+template <int W>
+__device__ void block_sort_store(uint64_t* kb, uint32_t* hist, uint32_t* ctl, uint32_t n, uint64_t span,
+                                 uint32_t idbits, uint32_t* dst_ids, int64_t* dst_d2, uint64_t base = 0) {
+    constexpr uint32_t nt = 64u * W, kPer = kLongCap / nt;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t sbits = span ? 64u - (uint32_t)__builtin_clzll(span) : 0u;
+    const uint32_t vs = min(sbits > 24u ? sbits - 24u : 0u, 63u - idbits);
+    const float scale = (float)n / ((float)(span >> vs) + 1.0f);
+    uint64_t key[kPer];
+    uint32_t bs[kPer];  // bucket | place in bucket << 16
     for (uint32_t t = tid; t < n; t += nt) hist[t] = 0u;
+    if (tid == 0) ctl[3] = 0u;
     __syncthreads();
-    for (uint32_t t = tid; t < n; t += nt) atomicAdd(&hist[sort_bucket(td[t], scale, n)], 1u);
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        const uint32_t t = tid + k * nt;
+        if (k * nt < n && t < n) {
+            key[k] = kb[t];
+            const uint32_t b = min((uint32_t)((float)(uint32_t)(key[k] >> (idbits + vs)) * scale), n - 1u);
+            bs[k] = b | (atomicAdd(&hist[b], 1u) << 16);
+        }
+    }
     __syncthreads();
     // bucket starts: each thread owns a run of buckets
-    const uint32_t per = (n + nt - 1) / nt, b0 = tid * per;
-    uint32_t sum = 0;
-    for (uint32_t k = 0; k < per; ++k)
-        if (b0 + k < n) sum += hist[b0 + k];
-    uint32_t run = block_scan_excl(sum, wsum);
-    for (uint32_t k = 0; k < per; ++k)
-        if (b0 + k < n) {
-            const uint32_t c = hist[b0 + k];
-            hist[b0 + k] = run;
-            run += c;
-        }
+    {
+        const uint32_t per = (n + nt - 1u) / nt, b0 = tid * per;
+        uint32_t sum = 0, most = 0;
+        for (uint32_t k = 0; k < per; ++k)
+            if (b0 + k < n) {
+                sum += hist[b0 + k];
+                most = max(most, hist[b0 + k]);
+            }
+        most = lane_val(scan_max(most), 63);
+        if ((tid & 63u) == 0) atomicMax(&ctl[3], most);
+        uint32_t run = block_scan_excl(sum, ctl + 4);
+        for (uint32_t k = 0; k < per; ++k)
+            if (b0 + k < n) {
+                const uint32_t c = hist[b0 + k];
+                hist[b0 + k] = run;
+                run += c;
+            }
+    }
     __syncthreads();
-    // scatter the indices by bucket: each bucket's cursor ends at the next
-    // one's start
-    for (uint32_t t = tid; t < n; t += nt) sx[atomicAdd(&hist[sort_bucket(td[t], scale, n)], 1u)] = t;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k)
+        if (k * nt < n && tid + k * nt < n) kb[hist[bs[k] & 0xFFFFu] + (bs[k] >> 16)] = key[k];
+    if (tid < kNearPad) {
+        // nothing before the first key is larger, nothing after the last smaller
+        kb[(int)tid - (int)kNearPad] = 0ull;
+        kb[n + tid] = ~0ull;
+    }
     __syncthreads();
+    const uint32_t near = ctl[3];  // keys of the fullest bucket
+    const uint64_t idm = (1ull << idbits) - 1ull;
     for (uint32_t t = tid; t < n; t += nt) {
-        const uint32_t i = sx[t];
-        const uint64_t d = td[i];
-        const uint32_t id = ti[i];
-        const uint32_t b = sort_bucket(d, scale, n);
-        const uint32_t lo = b ? hist[b - 1] : 0u, hi = hist[b];
-        uint32_t rank = lo;
-        for (uint32_t j = lo; j < hi; ++j) {
-            const uint32_t o = sx[j];
-            rank += key_less(td[o], ti[o], d, id) ? 1u : 0u;
+        const uint64_t kv = kb[t];
+        uint32_t rk = t;
+        if (near <= kNearPad + 1u) {
+            for (int d = 1; d < (int)near; ++d)
+                rk += (kb[(int)t + d] < kv ? 1u : 0u) - (kb[(int)t - d] > kv ? 1u : 0u);
+        } else {
+            for (uint32_t d = 1; d < near; ++d) {
+                if (t + d < n && kb[t + d] < kv) ++rk;
+                if (d <= t && kb[t - d] > kv) --rk;
+            }
         }
-        dst_ids[rank] = id;
-        if (dst_d2) dst_d2[rank] = (int64_t)(d + base);
+        dst_ids[rk] = (uint32_t)(kv & idm);
+        if (dst_d2) dst_d2[rk] = (int64_t)((kv >> idbits) + base);
     }
 }
 
-// A radius row of more than kLongCap pairs, by one block in two walks (write
-// pass): the first counts its hits per distance bucket (dist^2 >> sh, sh such
+// A radius row of more than kLongCap pairs (or whose keys do not pack), by one
+// block in two walks (write pass): the first counts its hits per distance bucket (dist^2 >> sh, sh such
 // that r^2 falls below kShellBuckets), the second writes each hit's sorted
 // position into the row's own output, grouped by bucket; then runs of buckets
 // of at most kShellCap pairs (shells, centre to edge) are read back into LDS,
 // their objects' distances computed again, ordered by the block sort and
 // stored in place.  The row needs no memory but its output.  Returns false,
 // with nothing written, when one bucket alone holds more than kShellCap pairs
-// (many objects at one distance): such a row is left to the windowed kernel.
+// (many objects at one distance) or spans more distances than pack with an id:
+// such a row is left to the windowed kernel.
 // What bounds it is the walk's and the block sort's instruction issue and LDS
 // traffic.  Before, every such row took one window of sort_cap pairs after
 // another on one wavefront, each window walking the whole row again: 512 rows
 // of about 20,000 pairs (20 objects per cell, 7 cells, clipped 32^3) took
 // 103 ms in all; now 0.65 ms.
-constexpr uint32_t kShellCap = 2560, kShellBuckets = 2048;
+constexpr uint32_t kShellCap = 2304, kShellBuckets = 2048;
 
-template <int METHOD>
+template <int METHOD, int W>
 __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, const AxisWrap& aw, const Query& s,
-                          int64_t rb, uint32_t rowlen, uint64_t* td, uint32_t* ti, uint32_t* sx, uint32_t* hist,
-                          uint32_t* bkt, uint32_t* own, uint32_t* ctl) {
+                          int64_t rb, uint32_t rowlen, uint32_t idbits, uint64_t* kb, uint32_t* hist, uint32_t* bkt,
+                          uint32_t* own, uint32_t* ctl) {
     const uint32_t tid = threadIdx.x, nt = blockDim.x, wave = tid >> 6, nw = nt >> 6;
     const uint32_t rbits = s.r2 ? 64u - (uint32_t)__builtin_clzll(s.r2) : 0u;
     const uint32_t sh = rbits > 11u ? rbits - 11u : 0u;  // kShellBuckets = 2^11
+    if (sh + idbits > 64u) return false;  // a bucket's distances do not pack with an id
+    // buckets whose distances, from the first's on, do
+    const uint32_t most_b = 64u - idbits - sh >= 11u ? kShellBuckets : 1u << (64u - idbits - sh);
     uint32_t cand = 0, walked = 0;
     auto walk_row = [&](auto&& visit) {
         walk<METHOD, false, false>(L, T, nullptr, s, false, walked, [&]() { return s.r2; },
@@ -3161,7 +3244,7 @@ __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, co
     __syncthreads();
     for (uint32_t b = 0, t0 = 0; t0 < rowlen;) {
         // the shell: buckets b .. e - 1, as many as fit
-        uint32_t lo = b + 1u, hi = kShellBuckets;  // the least e, the most
+        uint32_t lo = b + 1u, hi = min(kShellBuckets, b + most_b);  // the least e, the most
         while (lo < hi) {
             const uint32_t mid = (lo + hi + 1u) >> 1;
             if (bkt[mid - 1u] - t0 <= kShellCap)
@@ -3174,13 +3257,12 @@ __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, co
         const uint64_t span = min(s.r2, ((uint64_t)e << sh) - 1ull) - base;
         for (uint32_t t = tid; t < n; t += nt) {
             const uint4 P = L.pts[pos[t0 + t]];
-            td[t] = obj_dist2(aw, s, P) - base;
-            ti[t] = P.w;
+            kb[t] = ((obj_dist2(aw, s, P) - base) << idbits) | P.w;
         }
         __syncthreads();
         if (n > 0)
-            block_sort_store(td, ti, sx, hist, ctl + 4, n, span, A.out_ids + rb + t0,
-                             A.out_d2 ? A.out_d2 + rb + t0 : nullptr, base);
+            block_sort_store<W>(kb, hist, ctl, n, span, idbits, A.out_ids + rb + t0,
+                                A.out_d2 ? A.out_d2 + rb + t0 : nullptr, base);
         __syncthreads();
         t0 += n;
         b = e;
@@ -3193,32 +3275,41 @@ __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, co
 // setup expected to be long; the block counts the row, writes its size and,
 // when it holds at most kLongCap pairs and the stash has room, orders it into
 // the stash (one allocation per row) for the write pass to copy; otherwise
-// the row goes on the walk list like any row the count pass did not keep.
-template <int METHOD, bool COUNT>
-__global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A) {
+// the row goes on the big or the walk list like any row the count pass did not
+// keep.  The write pass's form takes the big list and the long-row list.
+// A row's hits are kept as keys dist^2 << idbits | id; one whose distances do
+// not leave room for an id is counted only, and ordered by shells.
+// A row is a chain of barriers with little work between them, so rows in flight
+// are what counts: 12 bytes of LDS per pair (keys, bucket counts) let four
+// blocks share a CU, where pairs with an index each, 20 bytes, let two: 16,400
+// rows of about 1,100 pairs (a service's batch of 65,536) took 528 us.
+template <int METHOD, bool COUNT, int W>
+__global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArgs A) {
     extern __shared__ __align__(16) char smem[];
-    uint64_t* td = (uint64_t*)smem;  // hits in arrival order
-    uint32_t* ti = (uint32_t*)(td + kLongCap);
-    uint32_t* sx = ti + kLongCap;    // their indices by bucket
-    uint32_t* hist = sx + kLongCap;
-    uint32_t* ctl = hist + kLongCap;  // [0] hits so far, [1] list entry taken, [2] stash offset, [4, 12) wave sums
-    const uint32_t wave = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = lane_id();
+    uint64_t* kb = (uint64_t*)smem + kNearPad;        // hits in arrival order
+    uint32_t* hist = (uint32_t*)(kb + kLongCap + kNearPad);
+    uint32_t* ctl = hist + kLongCap;  // [0] hits so far, [1] list entry taken, [2] stash offset, [3] fullest bucket,
+                                      // [4, 12) wave sums, [12] keys that do not pack
+    const uint32_t wave = threadIdx.x >> 6, nw = W, lane = lane_id();
     uint32_t* own = ctl + 16 + wave * 64;
-    static_assert(kShellCap * 20 + kShellBuckets * 4 <= kLongCap * 20, "a shell's buffers fit the row's");
+    static_assert(kShellCap * 12 + kShellBuckets * 4 <= kLongCap * 12, "a shell's buffers fit the row's");
     if (!COUNT && A.row_ptr[A.Q] > A.capacity) return;  // (the write kernel sets the flag)
+    const uint32_t nbig = COUNT ? 0u : uni(*A.big_count);
+    const uint32_t nq = nbig + uni(*A.list_count);
+    if (nq == 0) return;
     const AxisWrap aw = axis_wrap(L);
-    const uint32_t nq = uni(*A.list_count);
+    const uint32_t idbits = L.n > 1 ? 32u - (uint32_t)__builtin_clz(L.n - 1u) : 1u;
     uint32_t* qc = queue_set(A, (int)A.list_set);
     const uint32_t region = blockIdx.x % SPHIDX_NREGION;
     for (;;) {
         if (threadIdx.x == 0) {
             ctl[1] = atomicAdd(qc, 1u);
-            ctl[0] = 0u;
+            ctl[0] = ctl[12] = 0u;
         }
         __syncthreads();
         const uint32_t t = uni(ctl[1]);
         if (t >= nq) break;
-        const uint32_t qi = uni(A.list[t]);
+        const uint32_t qi = uni(t < nbig ? A.bigq[t] : A.list[t - nbig]);
         const Query s = load_query(L, A, qi);
         int64_t rb = 0;
         uint32_t rowlen = kLongCap;
@@ -3226,19 +3317,9 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
             rb = A.row_ptr[s.row];
             rowlen = (uint32_t)(A.row_ptr[s.row + 1] - rb);
         }
-        if (!COUNT && rowlen > kLongCap && (s.flags & (F_VALID | F_KNN | F_WINDOW)) == F_VALID) {
-            uint32_t* sti = (uint32_t*)(td + kShellCap);
-            uint32_t* ssx = sti + kShellCap;
-            uint32_t* shist = ssx + kShellCap;
-            if (!shell_row<METHOD>(L, T, A, aw, s, rb, rowlen, td, sti, ssx, shist, shist + kShellCap, own, ctl) &&
-                threadIdx.x == 0)
-                ((uint32_t*)(A.desc + 4 * (size_t)qi))[6] = s.flags | F_WINDOW;
-            __syncthreads();
-            continue;
-        }
         // the same for every wave of the block
-        const bool mine = (s.flags & F_VALID) && !(s.flags & F_KNN) && rowlen > 0 && rowlen <= kLongCap;
-        if (mine) {
+        const bool mine = (s.flags & F_VALID) && !(s.flags & (F_KNN | F_WINDOW)) && rowlen > 0;
+        if (mine && rowlen <= kLongCap) {
             uint32_t cand = 0, walked = 0;
             auto visit = [&](bool act, uint32_t p, const uint4& P) -> bool {
                 const uint64_t d2 = obj_dist2(aw, s, P);
@@ -3248,10 +3329,10 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
                     uint32_t base = 0;
                     if (lane == 0) base = atomicAdd(&ctl[0], (uint32_t)__popcll(hm));
                     base = uni(base);
-                    const uint32_t slot = base + lanes_below(hm);
+                    const uint32_t slot = lanes_below(hm, base);
                     if (hit && slot < kLongCap) {
-                        td[slot] = d2;
-                        ti[slot] = P.w;
+                        kb[slot] = (d2 << idbits) | P.w;
+                        if (d2 >> (64u - idbits)) ctl[12] = 1u;
                     }
                 }
                 return false;
@@ -3262,6 +3343,7 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
             }, 64u * wave, 64u * nw);
         }
         __syncthreads();
+        const bool packs = ctl[12] == 0u;
         if (COUNT) {
             const uint32_t n = (s.flags & F_VALID) ? ctl[0] : 0u;
             if (threadIdx.x == 0) {
@@ -3269,11 +3351,11 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
                 uint32_t off = 0u;  // empty rows: nothing to copy
                 if (n > 0) {
                     off = kMaxId;
-                    if (n <= kLongCap && A.stash) {
+                    if (n <= kLongCap && packs && A.stash) {
                         const uint32_t c = atomicAdd(A.stash_ctr + region * SPHIDX_QSTRIDE, n);
                         if ((uint64_t)c + n <= A.stash_region) off = region * A.stash_region + c;
                     }
-                    if (off == kMaxId) A.walkq[atomicAdd(A.walk_count, 1u)] = qi;
+                    if (off == kMaxId) list_row_again(A, qi, n > A.sort_cap);
                 }
                 A.soff[s.row] = off;
                 ctl[2] = off;
@@ -3281,11 +3363,18 @@ __global__ __launch_bounds__(512) void long_kernel(LatArgs L, TabArgs T, QArgs A
             __syncthreads();
             const uint32_t off = ctl[2];
             if (n > 0 && off != kMaxId)
-                block_sort_store(td, ti, sx, hist, ctl + 4, n, s.r2, A.stash_ids + off,
-                                 A.stash_d2 ? A.stash_d2 + off : nullptr);
+                block_sort_store<W>(kb, hist, ctl, n, s.r2, idbits, A.stash_ids + off,
+                                    A.stash_d2 ? A.stash_d2 + off : nullptr);
         } else if (mine) {
-            block_sort_store(td, ti, sx, hist, ctl + 4, min(ctl[0], rowlen), s.r2, A.out_ids + rb,
-                             A.out_d2 ? A.out_d2 + rb : nullptr);
+            if (rowlen <= kLongCap && packs) {
+                block_sort_store<W>(kb, hist, ctl, min(ctl[0], rowlen), s.r2, idbits, A.out_ids + rb,
+                                    A.out_d2 ? A.out_d2 + rb : nullptr);
+            } else {
+                uint32_t* bkt = (uint32_t*)(kb + kShellCap + kNearPad);
+                if (!shell_row<METHOD, W>(L, T, A, aw, s, rb, rowlen, idbits, kb, bkt + kShellBuckets, bkt, own, ctl) &&
+                    threadIdx.x == 0)
+                    ((uint32_t*)(A.desc + 4 * (size_t)qi))[6] = s.flags | F_WINDOW;
+            }
         }
         __syncthreads();
     }
@@ -3502,6 +3591,12 @@ hipError_t launch_copy(const QArgs& q, const LatArgs& L, hipStream_t st) {
 #define SPHIDX_PICKP(KERNEL, variant, SPH, ...) \
     ((variant) == 3 ? (const void*)KERNEL<kPaper, false __VA_ARGS__> : SPHIDX_PICK(KERNEL, variant, SPH, __VA_ARGS__))
 
+// The block-per-row kernel by its waves.
+#define SPHIDX_LONG(METHOD, COUNT, w)                        \
+    ((w) == 2   ? (const void*)long_kernel<METHOD, COUNT, 2> \
+     : (w) == 4 ? (const void*)long_kernel<METHOD, COUNT, 4> \
+                : (const void*)long_kernel<METHOD, COUNT, 8>)
+
 // Small batches, where launches and not work are what a call costs: up to
 // kSmallSetup queries one block clears the counters and sets up every query,
 // and up to kMergedQ the main kernels walk the fallback queries too, instead of
@@ -3542,7 +3637,9 @@ int device_cu_count() {
     return cus;
 }
 
-size_t long_lds_bytes(uint32_t waves) { return (size_t)kLongCap * 20 + 64 + (size_t)waves * 256; }
+size_t long_lds_bytes(uint32_t waves) {
+    return (size_t)(kLongCap + 2 * kNearPad) * 8 + (size_t)kLongCap * 4 + 64 + (size_t)waves * 256;
+}
 
 // LDS bytes per block: pass 0 count (3 with the stash), 1 write, 2 top-M,
 // 4 grouped count (5 with the stash).
@@ -3572,13 +3669,13 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
     // one block per long radius row (count pass: the rows the setup listed;
     // write pass: rows longer than a wavefront's buffer)
     auto launch_long = [&](bool count, const QArgs& qa) -> hipError_t {
-        const void* lf =
-            count ? (variant == 0   ? (const void*)long_kernel<kCube, true>
-                     : variant == 3 ? (const void*)long_kernel<kPaper, true>
-                                    : (const void*)long_kernel<kEither, true>)
-                  : (variant == 0   ? (const void*)long_kernel<kCube, false>
-                     : variant == 3 ? (const void*)long_kernel<kPaper, false>
-                                    : (const void*)long_kernel<kEither, false>);
+        const uint32_t lw = qa.long_waves;
+        const void* lf = count ? (variant == 0   ? SPHIDX_LONG(kCube, true, lw)
+                                  : variant == 3 ? SPHIDX_LONG(kPaper, true, lw)
+                                                 : SPHIDX_LONG(kEither, true, lw))
+                               : (variant == 0   ? SPHIDX_LONG(kCube, false, lw)
+                                  : variant == 3 ? SPHIDX_LONG(kPaper, false, lw)
+                                                 : SPHIDX_LONG(kEither, false, lw));
         const size_t lds = long_lds_bytes(qa.long_waves);
         const uint32_t per_cu = (uint32_t)std::max<size_t>(1, (160u * 1024u) / lds);
         LatArgs l = L;

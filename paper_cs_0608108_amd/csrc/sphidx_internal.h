@@ -138,6 +138,8 @@ struct QArgs {
     uint32_t* xq;       // grouped count: queries left to the one-query-per-wave kernel
     uint32_t* lq_count;
     uint32_t* lq;       // stash mode: radius rows expected to be long, counted one block per row
+    uint32_t* big_count;
+    uint32_t* bigq;     // stash mode: rows not kept that go to the block-per-row and top-M kernels
     uint32_t* item_count;  // tile count: its work items (kept in longq, free until later launches)
     uint32_t* soff;     // stash mode: per output row, first stash element of its sorted row
     uint32_t* stash_hdr;  // stash header written by the count pass (see StashHdr)
@@ -179,7 +181,7 @@ enum : uint32_t { kHdrMode = 0, kHdrElems = 1, kHdrHasD2 = 2, kHdrD2Off = 3, kHd
 #define SPHIDX_NREGION SPHIDX_NXCD  // stash regions, one per XCD
 #define SPHIDX_QSTRIDE 32       // counters 128 bytes apart: one L2 line each
 #define SPHIDX_NQSETS 7         // count, write, top-M, fallback count, fallback write, walk list, extra list
-#define SPHIDX_NLISTS 7         // long_count, fb_count, walk_count, stash header, xq_count, lq_count, item_count
+#define SPHIDX_NLISTS 8  // long_count, fb_count, walk_count, stash header, xq_count, lq_count, item_count, big_count
 #define SPHIDX_COUNTER_WORDS \
     ((SPHIDX_NQSETS * SPHIDX_NQUEUE + SPHIDX_NLISTS + SPHIDX_NREGION) * SPHIDX_QSTRIDE)
 #define SPHIDX_MAX_LOG2_SUM 30
