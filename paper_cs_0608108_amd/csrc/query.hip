@@ -59,6 +59,8 @@ __device__ __forceinline__ uint32_t lane_id() {
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t base = 0u) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
 }
+// This lane's bit of a wave mask, as a predicate.
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 __device__ __forceinline__ uint32_t bperm(uint32_t v, uint32_t lane) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)v);
 }
@@ -1610,6 +1612,26 @@ constexpr uint32_t kMaxHitCap = 256 * kHitEighths / 8;
 // 1.154; 1.5 x 1.092, 1.25 x 1.062; keeping the leading queries, 1.25 x
 // 1.028, 1 x 1.006 (0.988 within 80 VGPRs), 7/8 x 1.039; rows up to 7/8 of
 // sort_cap at 1 x, 1.004.
+// A K-NN slot counts for its expected hits, 9/8 knn_target(K), where its rows
+// are more: rows stand for hits only at about one object per cell, and on a
+// sparse cloud a claim of eight queries broke into groups of six and two, the
+// short one almost as long as the other (98,765 points at 0.38 per cell, K =
+// 10: count pass 0.263 -> 0.249 ms).  Radius slots count for their rows: by
+// their ball at the lattice's mean density, the uneven-radius workload's
+// count pass took 0.691 ms instead of 0.675.
+//
+// Bound by instruction issue (some 2,000 vector instructions per group of
+// eight, spread over row geometry, candidates and the ordering) and, at six
+// waves per SIMD, by waiting.  A candidate finds its row by counting the bits
+// below its lane, two instructions where a max-scan over marks took ten, and
+// the keys and their buckets stay in registers from the first pass of the
+// ordering to the rank.  Count pass, ms, before and after these: 4,194,304
+// clustered points, K = 16, 2.62 -> 2.58; 1,048,576 uneven radii 0.683 ->
+// 0.666; 1,869,073 uniform points, K = 1, 0.406 -> 0.400.  The distance in
+// doubles (as in the tiles) saves nine issue slots per step but needs nine
+// more registers than there are: 2.57 against 2.53 and 0.692 against 0.676 in
+// the same build; noting slot ends by scalar code, only where the slot
+// changes, was no faster, and slower where runs are short.
 
 // Per-wave LDS of the grouped kernel: slot data (kGroup x 80 B), 32 words of
 // per-slot counters, the 64-word owner map, then (stash) the hit keys in
@@ -1624,7 +1646,6 @@ __host__ __device__ constexpr uint32_t group_chunk(uint32_t cap) {
 }
 // 64-row layers of the largest chunk (sort_cap 256)
 constexpr uint32_t kLayers = (group_chunk(256) + 63) / 64;
-static_assert(kLayers * 64 + 1 <= 255, "candidate-step owner marks hold a chunk row + 1 in one byte");
 __host__ __device__ constexpr size_t group_lds_per_wave(bool stash, uint32_t cap) {
     return 640 + 128 + 256 + (stash ? (size_t)group_hitcap(cap) * 20 : (size_t)group_chunk(cap) * 16);
 }
@@ -1723,9 +1744,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                 }
             }
             {
-                const uint32_t pre_incl = scan_add(rows);
+                // a K-NN slot counts for its rows or for the hits it is
+                // expected to bring, whichever is less (see kRowEighths)
+                const uint32_t load =
+                    KNN && knn ? min(rows, (uint32_t)(1.125f * knn_target((float)d1.y)) + 1u) : rows;
+                const uint32_t pre_incl = scan_add(load);
                 const uint64_t fits = __ballot(lane < cand && pre_incl <= rlim);
                 ng = max(1u, (uint32_t)__popcll(fits));
+                if (lane < kGroup) qst[lane] = pre_incl;  // (free until the sort)
             }
             if (lane >= ng) {
                 rows = 0;
@@ -1760,10 +1786,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
             const uint32_t CH = group_chunk(A.sort_cap);  // <= kLayers x 64
             for (uint32_t rb = 0; rb < R; rb += CH) {
                 const uint32_t clen = min(CH, R - rb);
-                uint32_t cex[kLayers], cin[kLayers];
+                uint32_t cex[kLayers];  // where the lane's rows start in the stream (~0: no candidates)
 #pragma unroll
-                for (uint32_t k = 0; k < kLayers; ++k) cex[k] = cin[k] = 0u;
-                uint32_t carry = 0;
+                for (uint32_t k = 0; k < kLayers; ++k) cex[k] = ~0u;
+                uint32_t carry = 0, kept_rows = 0;
                 for (uint32_t k = 0; k * 64u < clen; ++k) {
                     // ---- this lane's row: owner slot and entry
                     const uint32_t base = rb + k * 64u;
@@ -1827,51 +1853,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                     const uint32_t tl = act ? r.cnt0 + r.cnt1 : 0u;
                     const uint32_t ci = scan_add(tl);
                     const uint32_t ce = carry + ci - tl;
-                    // per row: position bases of its two ranges, the slot
-                    // where the second starts, and the query slot
-                    if (act) rinfo[k * 64u + lane] = make_uint4(r.st0 - ce, ce + r.cnt0, r.st1 - (ce + r.cnt0), gs);
+                    // per row with candidates, in order: position bases of its
+                    // two ranges, the slot where the second starts, and the
+                    // query slot
+                    const uint64_t full = __builtin_amdgcn_ballot_w64(tl > 0u);
+                    if (tl > 0u)
+                        rinfo[lanes_below(full, kept_rows)] =
+                            make_uint4(r.st0 - ce, ce + r.cnt0, r.st1 - (ce + r.cnt0), gs);
+                    kept_rows += (uint32_t)__popcll(full);
 #pragma unroll
-                    for (uint32_t j = 0; j < kLayers; ++j) {
-                        cex[j] = j == k ? ce : cex[j];
-                        cin[j] = j == k ? ce + tl : cin[j];
-                    }
+                    for (uint32_t j = 0; j < kLayers; ++j) cex[j] = j == k && tl > 0u ? ce : cex[j];
                     carry += lane_val(ci, 63);
                 }
                 const uint32_t CT = carry;
-                // ---- owner row of each of the 64 slots from cb: a row marks
-                // where its range starts in the step (a row begun earlier
-                // marks slot 0), and a max-scan hands every slot to its row
-                // The marks cover a window of four steps (256 slots, one
-                // byte each in the owner map's words): rows are marked once
-                // per window, and each step max-scans its 64 bytes on top of
-                // the owner the window's earlier steps ended with.  Steps are
-                // located in order, each once.
-                uint8_t* own8 = (uint8_t*)own;
-                uint32_t wcarry = 0;
-                auto locate = [&](uint32_t cb, uint32_t& pos, uint32_t& sl) -> bool {
-                    const uint32_t wb = cb & ~255u, wo = cb - wb;
-                    if (wo == 0) {
+                // ---- owner row of each of the 64 slots from cb: every row
+                // marks the slot where it starts, in a window of four steps
+                // (256 slots, one byte each in the owner map's words); a
+                // slot's row is the number of marks up to its own, counted on
+                // from the rows before.  Steps are located in order, each
+                // once.  (One bit per slot, for 2,048 slots at a time, needs
+                // no read per step, but rows of a candidate or two meet in
+                // one word's atomics: 4 % slower on a K = 1 cloud.)
+                uint32_t before = 0;
+                auto locate = [&](uint32_t cb, uint32_t& pos, uint32_t& sl) {
+                    const uint32_t wb = cb & ~255u;
+                    uint8_t* own8 = (uint8_t*)own;
+                    if (cb == wb) {
                         wave_sync();
                         own[lane] = 0;
                         wave_sync();
 #pragma unroll
                         for (uint32_t k = 0; k < kLayers; ++k)
-                            if (cin[k] > cex[k] && cex[k] < wb + 256u && cin[k] > wb)
-                                own8[cex[k] > wb ? cex[k] - wb : 0] = (uint8_t)(k * 64u + lane + 1u);
+                            if (cex[k] - wb < 256u) own8[cex[k] - wb] = 1u;
                         wave_sync();
-                        wcarry = 0;
                     }
-                    const uint32_t m = max(scan_max((uint32_t)own8[wo + lane]), wcarry);
-                    wcarry = lane_val(m, 63);
-                    // (a step past the end marks nothing: row 0 stands in)
-                    const uint32_t o = max(m, 1u) - 1u;
-                    const uint4 ri = rinfo[o];
+                    const uint64_t mk = __builtin_amdgcn_ballot_w64(own8[cb - wb + lane] != 0);
+                    const uint4 ri = rinfo[lanes_below(mk >> 1, before + (uint32_t)(mk & 1u) - 1u)];
+                    before += (uint32_t)__popcll(mk);
                     const uint32_t g = cb + lane;
-                    pos = (g < ri.y ? ri.x : ri.z) + g;
+                    // (slots past the end: the last row's, held inside the array)
+                    pos = min((g < ri.y ? ri.x : ri.z) + g, L.n - 1u);
                     sl = ri.w;
-                    return g < CT;
                 };
-                auto test = [&](const uint4& P, uint32_t pos, uint32_t sl, bool cact, uint32_t cb) {
+                auto test = [&](const uint4& P, uint32_t pos, uint32_t sl, uint32_t cb) {
                     const uint4 ch = qp[4 * kGroup + sl];
                     const uint2 cr = *(const uint2*)(qp + kGroup + sl);
                     const uint32_t pv[3] = {P.x, P.y, P.z}, hv[3] = {ch.x, ch.y, ch.z};
@@ -1881,38 +1905,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                         const int32_t dd = (int32_t)((pv[a] + hv[a]) & aw.mask[a]) - (int32_t)aw.half[a];
                         d2 += (uint64_t)((int64_t)dd * dd);
                     }
-                    const uint64_t r2 = (uint64_t)cr.x | ((uint64_t)cr.y << 32);
-                    const bool hit = cact && d2 <= r2 && pos != ch.w;
-                    if (A.stats && cact) atomicAdd(A.stats + 4 * (size_t)qp[3 * kGroup + sl].w + 2, 1u);
-                    const uint64_t H = __ballot(hit);
-                    const uint32_t hp = hcount + lanes_below(H);
+                    const uint64_t in = CT - cb >= 64u ? ~0ull : (1ull << (CT - cb)) - 1ull;
+                    const uint64_t H = in & __builtin_amdgcn_ballot_w64(d2 <= ((uint64_t)cr.x | ((uint64_t)cr.y << 32))) &
+                                       __builtin_amdgcn_ballot_w64(pos != ch.w);
+                    if (A.stats && lane_in(in)) atomicAdd(A.stats + 4 * (size_t)qp[3 * kGroup + sl].w + 2, 1u);
+                    const uint32_t hp = lanes_below(H, hcount);
                     // hits per slot: a slot's candidates take contiguous lanes
                     // and its hits arrive in order, so the last lane of its
                     // run in a step records the group's hit count so far
+                    // (lanes past the end belong to the last row's slot)
                     const uint32_t nsl = bperm(sl, (lane + 1u) & 63u);
-                    if (cact && (lane == 63u || cb + lane + 1u >= CT || nsl != sl)) cnt[sl] = hp + (hit ? 1u : 0u);
-                    if (STASH && hit && hp < hitcap)
-                        hb[hp] = ((uint64_t)sl << (64u - kGroupBits)) | (d2 << idbits) | (uint64_t)P.w;
+                    if (lane == 63u || nsl != sl) cnt[sl] = hp + (lane_in(H) ? 1u : 0u);
+                    if (STASH && lane_in(H) && hp < hitcap) {
+                        const uint64_t k = d2 << idbits;
+                        hb[hp] = ((uint64_t)((sl << (32u - kGroupBits)) | (uint32_t)(k >> 32)) << 32) |
+                                 ((uint32_t)k | P.w);
+                    }
                     hcount += (uint32_t)__popcll(H);
                 };
                 if (CT > 0) {
                     // two register sets taken in turn: the step after the one
-                    // under test is already loading.  Lanes past the end load
-                    // record 0 (present whenever a candidate is) and test
-                    // nothing.
+                    // under test is already loading (the one past the end,
+                    // located once per chunk, reads a record and tests nothing)
                     uint32_t pa = 0, sa = 0, pb = 0, sb = 0;
-                    bool aa = locate(0, pa, sa), ab = false;
-                    uint4 PA = L.pts[aa ? pa : 0u], PB = PA;
-                    // (the step past the end, located once per chunk, has no
-                    // active lane)
+                    locate(0, pa, sa);
+                    uint4 PA = L.pts[pa], PB = PA;
                     for (uint32_t cb = 0; cb < CT; cb += 128) {
-                        ab = locate(cb + 64, pb, sb);
-                        PB = L.pts[ab ? pb : 0u];
-                        test(PA, pa, sa, aa, cb);
+                        locate(cb + 64, pb, sb);
+                        PB = L.pts[pb];
+                        test(PA, pa, sa, cb);
                         if (cb + 64 >= CT) break;
-                        aa = locate(cb + 128, pa, sa);
-                        PA = L.pts[aa ? pa : 0u];
-                        test(PB, pb, sb, ab, cb + 64);
+                        locate(cb + 128, pa, sa);
+                        PA = L.pts[pa];
+                        test(PB, pb, sb, cb + 64);
                     }
                 }
                 wave_sync();
@@ -1938,7 +1963,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                 total = lane_val(hi, ng - 1u);
                 // later groups of this wave take no more rows than fitted
                 // here, and grow back by an eighth per group that fits
-                rlim = max(1u, lane_val(incl, ng - 1u));
+                rlim = max(1u, uni(qst[ng - 1u]));
             } else if (STASH) {
                 rlim = min(grows, rlim + max(1u, grows / 8u));
             }
@@ -2037,12 +2062,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                         return qst[sl] + bi;
                     };
                     uint32_t slot[(kMaxHitCap + 63) / 64], bk[(kMaxHitCap + 63) / 64];
+                    uint64_t kv[(kMaxHitCap + 63) / 64];
 #pragma unroll
                     for (uint32_t k = 0; k < (kMaxHitCap + 63) / 64; ++k) {
                         const uint32_t t = lane + 64u * k;
                         bk[k] = 0u;
                         if (t < total) {
-                            bk[k] = bucket(hb[t]);
+                            kv[k] = hb[t];
+                            bk[k] = bucket(kv[k]);
                             slot[k] = atomicAdd(&hh[bk[k]], 1u);
                         }
                     }
@@ -2064,12 +2091,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
 #pragma unroll
                     for (uint32_t k = 0; k < (kMaxHitCap + 63) / 64; ++k) {
                         const uint32_t t = lane + 64u * k;
-                        if (t < total) hs[hh[bk[k]] + slot[k]] = hb[t];
+                        if (t < total) hs[hh[bk[k]] + slot[k]] = kv[k];
                     }
                     wave_sync();
-                    for (uint32_t t = lane; t < total; t += 64) {
-                        const uint64_t key = hs[t];
-                        const uint32_t bi = bucket(key);
+#pragma unroll
+                    for (uint32_t k = 0; k < (kMaxHitCap + 63) / 64; ++k) {
+                        const uint32_t t = lane + 64u * k;
+                        if (t >= total) continue;
+                        const uint64_t key = kv[k];
+                        const uint32_t bi = bk[k];
                         const uint32_t lo = hh[bi], hi = bi + 1 < total ? hh[bi + 1] : total;
                         uint32_t rank = lo;
                         for (uint32_t j = lo; j < hi; ++j) rank += hs[j] < key ? 1u : 0u;
@@ -2261,8 +2291,6 @@ __device__ __forceinline__ void swap_rows16(double& a, double& b) {
     b = __hiloint2double((int)bh, (int)bl);
 }
 
-// This lane's bit of a wave mask, as a predicate.
-__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 // v plus this lane's bit of a wave mask (one add with the mask as carry).
 __device__ __forceinline__ uint32_t add_bit(uint32_t v, uint64_t m) {
     uint32_t r;
