@@ -16,10 +16,13 @@ namespace {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;  // per thread
 constexpr int kScanBlock = kScanThreads * kScanItems;
+constexpr uint32_t kScanSumBlocks = 8192;
 
-__global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t v, size_t n) {
+// p[0 .. n) = v and, with `word`, *word = w.
+__global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t v, size_t n, uint32_t* word, uint32_t w) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     size_t stride = (size_t)gridDim.x * blockDim.x;
+    if (word && i == 0) *word = w;
     for (; i < n; i += stride) p[i] = v;
 }
 
@@ -199,7 +202,12 @@ __global__ __launch_bounds__(256) void cell_list_kernel(BuildArgs a, const uint3
 
 // ---------------------------------------------------------------------------
 // Exclusive scan, reduce-then-scan over blocks of kScanBlock elements.
-// No inter-block waiting: three launches, each block independent.
+// No inter-block waiting: each block is independent.  Up to kScanSumBlocks
+// blocks, two launches: a down-sweep block adds up the totals before its own
+// (at most 32 loads per thread, from L2); past that the totals are scanned by
+// one block in between.  A whole rebuild of 2,000 objects, us, with the scan
+// in between and without: 19.9 and 17.8 at 9 blocks, 26.3 and 24.4 at 513,
+// 79.4 and 69.2 at 4,097; 528 and 572 at 32,769.
 
 template <typename T>
 __device__ T block_exclusive_scan(T v, T* sh, T& total) {
@@ -268,7 +276,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_partials_kernel(T* __restri
 // Each thread scans its own run of kScanItems elements of `in` into `out`
 // (the same array for an in-place scan); with VEC (both 16-byte aligned) a
 // whole run is moved with 16-byte loads and stores.
-template <typename T, bool VEC>
+template <typename T, bool VEC, bool SUM>
 __global__ __launch_bounds__(kScanThreads) void scan_down_kernel(const T* in, T* out, size_t n,
                                                                  const T* __restrict__ partial, uint32_t nb) {
     __shared__ T sh[kScanThreads / 64 + 1];
@@ -290,7 +298,16 @@ __global__ __launch_bounds__(kScanThreads) void scan_down_kernel(const T* in, T*
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) s += v[k];
     T tot;
-    T off = block_exclusive_scan<T>(s, sh, tot) + partial[blockIdx.x];
+    T off = block_exclusive_scan<T>(s, sh, tot);
+    T before = 0;  // everything in the blocks before this one
+    if (SUM) {
+        T t = 0;
+        for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kScanThreads) t += partial[b];
+        block_exclusive_scan<T>(t, sh, before);
+    } else {
+        before = partial[blockIdx.x];
+    }
+    off += before;
     T o[kScanItems];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -308,7 +325,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_down_kernel(const T* in, T*
         for (int k = 0; k < kScanItems; ++k)
             if (base + k < n) out[base + k] = o[k];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = partial[nb];
+    if (blockIdx.x == nb - 1u && threadIdx.x == 0) out[n] = before + tot;
 }
 
 // Short arrays in one launch: one block takes the chunks of kScanBlock
@@ -352,11 +369,12 @@ hipError_t scan_exclusive_to(const T* in, T* out, size_t n, T* partial, hipStrea
         return hipGetLastError();
     }
     scan_reduce_kernel<T><<<nb, kScanThreads, 0, st>>>(in, n, partial);
-    scan_partials_kernel<T><<<1, kScanThreads, 0, st>>>(partial, nb);
-    if ((((uintptr_t)in | (uintptr_t)out) & 15u) == 0)
-        scan_down_kernel<T, true><<<nb, kScanThreads, 0, st>>>(in, out, n, partial, nb);
-    else
-        scan_down_kernel<T, false><<<nb, kScanThreads, 0, st>>>(in, out, n, partial, nb);
+    const bool sum = nb <= kScanSumBlocks;
+    if (!sum) scan_partials_kernel<T><<<1, kScanThreads, 0, st>>>(partial, nb);
+    const bool vec = (((uintptr_t)in | (uintptr_t)out) & 15u) == 0;
+    auto down = vec ? (sum ? scan_down_kernel<T, true, true> : scan_down_kernel<T, true, false>)
+                    : (sum ? scan_down_kernel<T, false, true> : scan_down_kernel<T, false, false>);
+    down<<<nb, kScanThreads, 0, st>>>(in, out, n, partial, nb);
     return hipGetLastError();
 }
 
@@ -367,11 +385,11 @@ hipError_t scan_exclusive(T* data, size_t n, T* partial, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t st) {
+hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t st, uint32_t* word, uint32_t word_value) {
     if (n == 0) return hipSuccess;
     size_t blocks = (n + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    fill_u32_kernel<<<(uint32_t)blocks, 256, 0, st>>>(p, value, n);
+    fill_u32_kernel<<<(uint32_t)blocks, 256, 0, st>>>(p, value, n, word, word_value);
     return hipGetLastError();
 }
 
@@ -416,11 +434,10 @@ hipError_t launch_build(const sphidx_lattice* lat, const uint32_t* x, const uint
                         uint32_t n, hipStream_t st) {
     const BuildArgs a = build_args(lat, x, y, z, n);
     size_t ncount = (size_t)lat->ncells + 2;
-    hipError_t e = launch_fill_u32(lat->cell_start, 0u, ncount + 1, st);
-    if (e != hipSuccess) return e;
     const bool xo = lat->cell_order == SPHIDX_ORDER_X;
-    // the x-order word: set here, cleared by a cell too large to order
-    if ((e = launch_fill_u32(lat->status + 1, xo ? 1u : 0u, 1, st)) != hipSuccess) return e;
+    // counts, and the x-order word: set here, cleared by a cell too large to order
+    hipError_t e = launch_fill_u32(lat->cell_start, 0u, ncount + 1, st, lat->status + 1, xo ? 1u : 0u);
+    if (e != hipSuccess) return e;
     uint32_t blocks = (n + 255) / 256;
     if (n > 0) hist_kernel<<<blocks, 256, 0, st>>>(a);
     e = scan_exclusive<uint32_t>(lat->cell_start, ncount, lat->scan_tmp, st);
@@ -466,10 +483,9 @@ hipError_t launch_build_records(const sphidx_lattice* lat, const uint4* recs, ui
     BuildArgs a = build_args(lat, nullptr, nullptr, nullptr, n);
     a.recs = recs;
     size_t ncount = (size_t)lat->ncells + 2;
-    hipError_t e = launch_fill_u32(lat->cell_start, 0u, ncount + 1, st);
+    // counts, and the x-order word: cells in the counting sort's order
+    hipError_t e = launch_fill_u32(lat->cell_start, 0u, ncount + 1, st, lat->status + 1, 0u);
     if (e != hipSuccess) return e;
-    // cells in the counting sort's order
-    if ((e = launch_fill_u32(lat->status + 1, 0u, 1, st)) != hipSuccess) return e;
     uint32_t blocks = (n + 255) / 256;
     if (n > 0) hist_records_kernel<<<blocks, 256, 0, st>>>(a);
     e = scan_exclusive<uint32_t>(lat->cell_start, ncount, lat->scan_tmp, st);

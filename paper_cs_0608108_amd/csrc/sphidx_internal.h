@@ -201,7 +201,9 @@ void paper_tables_flat(int m, std::vector<uint32_t>& off, std::vector<uint32_t>&
 // ---------------------------------------------------------------------------
 // Launchers (defined in the .hip files).
 
-hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t st);
+// p[0 .. n) = value and, with `word`, *word = word_value, in one launch
+hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t st, uint32_t* word = nullptr,
+                           uint32_t word_value = 0u);
 hipError_t launch_build(const sphidx_lattice* lat, const uint32_t* x, const uint32_t* y, const uint32_t* z,
                         uint32_t n, hipStream_t st);
 hipError_t launch_cell_list(const sphidx_lattice* lat, hipStream_t st);

@@ -178,8 +178,10 @@ __global__ __launch_bounds__(256) void inc_move_kernel(MoveArgs m, IncArgs a) {
     if (!st) a.arank[p] = atomicAdd(&a.cnt[c2], 1u);
 }
 
-__global__ __launch_bounds__(256) void inc_count_kernel(IncArgs a) {
+// (the step counter, with `step`, advances here: the objects have moved)
+__global__ __launch_bounds__(256) void inc_count_kernel(IncArgs a, uint32_t* step) {
     const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (step && c == 0u) *step += 1u;
     if (c >= a.ncells + 2u) return;
     const uint32_t b = a.stay[a.cs[c]], e = a.stay[a.cs[c + 1]];
     a.sb[c] = b;
@@ -300,16 +302,14 @@ hipError_t launch_move_incremental(sphidx_lattice* lat, uint64_t seed, uint32_t 
     a.cs = lat->cell_start;
     a.stay = lat->rank;
     const MoveArgs m = move_args(lat->desc, seed, step, step_dev, n);
-    hipError_t e = launch_fill_u32(a.cnt, 0u, (size_t)lat->ncells + 3, st);
+    // (the status word: arrivals follow the stayers, cells in no particular order)
+    hipError_t e = launch_fill_u32(a.cnt, 0u, (size_t)lat->ncells + 3, st, lat->status + 1, 0u);
     if (e != hipSuccess) return e;
-    // arrivals follow the stayers: cells in no particular order
-    if ((e = launch_fill_u32(lat->status + 1, 0u, 1, st)) != hipSuccess) return e;
     const uint32_t blocks = (n + 255) / 256;
     if (n > 0) inc_move_kernel<<<blocks, 256, 0, st>>>(m, a);
-    if (step_dev) advance_step_kernel<<<1, 1, 0, st>>>(step_dev);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_scan_u32(a.stay, n, lat->scan_tmp, st)) != hipSuccess) return e;
-    inc_count_kernel<<<(lat->ncells + 2u + 255u) / 256u, 256, 0, st>>>(a);
+    inc_count_kernel<<<(lat->ncells + 2u + 255u) / 256u, 256, 0, st>>>(a, step_dev);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the new counts' scan is written straight into the lattice's cell starts
     if ((e = launch_scan_u32_to(a.cnt, lat->cell_start, (size_t)lat->ncells + 2, lat->scan_tmp, st)) != hipSuccess)
