@@ -421,7 +421,7 @@ def leg_timestep(args, out):
     alg = query_bytes(n, ncells, n, pairs)
     upd = resident_update_bytes(n, ncells)
     step_alg = upd["move"] + upd["rebuild"] + alg
-    rl = roofline(w.name, ("group_count_kernel" if cfg.get("grouped") else "count_kernel")
+    rl = roofline(w.name, ("tile_count_kernel" if cfg.get("grouped") else "count_kernel")
                   + " (walk, test, sort, keep rows)", alg, kern_ms, out.get("hbm_copy_GBps"),
                   {"step": {"algorithmic_bytes": int(step_alg), "ms": round(ms, 4),
                             "achieved": round(step_alg / (ms * 1e-3) / 1e9, 2),

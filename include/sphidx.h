@@ -260,10 +260,10 @@ typedef struct {
 } sphidx_csr;
 
 /* The stash.  Workspace bytes beyond the minimum let the count pass keep
- * each radius row of at most sort_cap objects, and each K-NN row of K <= 64
- * (searched there to the end), already sorted, so that the write pass copies
- * it into place instead of walking the tables again.  A
- * row needs 4 bytes per object (12 when the count call passes dist2_dev).
+ * each radius row of at most sort_cap objects, each longer one that a block
+ * counts (long_row_waves), and each K-NN row of K <= 64 (searched there to
+ * the end), already sorted, so that the write pass copies it into place
+ * instead of walking the tables again.  A row needs 4 bytes per object (12 when the count call passes dist2_dev).
  * Rows that do not fit are walked again by the write pass, so any size is
  * correct; sphidx_query_stash_bytes gives the size that keeps every row.
  * The write pass must use the workspace the count pass used, unchanged.
@@ -360,10 +360,11 @@ typedef struct {
     uint32_t* method_dev;     /* optional uint32[Q], written by the count pass: the walk each query
                                  used (SPHIDX_METHOD_SPHERE, _CUBE or _LIST), or 0xFFFFFFFF for a
                                  query with an empty row by definition (invalid centre, K = 0) */
-    uint32_t long_row_waves;  /* write pass, radius rows longer than sort_cap and at most 3072 pairs:
-                                 the wavefronts that walk and order one such row together, as one
-                                 block (2, 4 or 8; 0 = 4); 1 = one wavefront per row, which takes
-                                 the row in windows of sort_cap, walking it once per window */
+    uint32_t long_row_waves;  /* radius rows longer than sort_cap: the wavefronts that walk and order
+                                 one such row together, as one block (2, 4 or 8; 0 = 4), a row past
+                                 the block's buffer in shells of distance; 1 = one wavefront per row,
+                                 which takes the row in windows of sort_cap, walking it once per
+                                 window (as do rows whose pairs crowd at one distance) */
 } sphidx_launch;
 
 /* Bytes of device scratch a query call on Q queries needs. */

@@ -22,13 +22,16 @@
 //           stopping once K are found); with workspace to spare it also
 //           sorts each radius row by (dist^2, id) and keeps it (the stash),
 //           and the write pass only copies the kept rows into place.  Rows
-//           not kept are walked again by the write pass.  K-NN rows and
-//           long rows go to the top-M kernel, which keeps the M best (in
-//           registers for M <= 64), shrinks the bound to the M-th distance
-//           once M are held and stops at the first row whose key exceeds it
-//           (Section II.A, K nearest).
+//           not kept are walked again by the write pass.  Long radius rows
+//           take one block each.  K-NN rows not kept go to the top-M
+//           kernel, which keeps the M best (in registers for M <= 64),
+//           shrinks the bound to the M-th distance once M are held and
+//           stops at the first row whose key exceeds it (Section II.A, K
+//           nearest).
 // The count pass can also take radius queries in groups of several per
-// wavefront, so that short rows and small radii fill whole steps.  Queries
+// wavefront, so that short rows and small radii fill whole steps, and
+// all-agents queries of one radius by tiles of space, their pairs on the
+// matrix cores.  Queries
 // whose radius exceeds the tables' cap or the cyclic limit, or whose centre
 // is outside the region, and every query of the cube method, scan the
 // bin-lattice bounding cube instead (Section I; Section III.B).  With the
