@@ -2175,6 +2175,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
 // queries per group, pairs of its hit buffer, rows per chunk of the walk,
 // candidates of the ring (a power of two, at least 63 + 64), cells per strip
 // chunk, queries per work item
+constexpr uint32_t kTileMinQ = 1024;  // the smallest batch by tiles
 constexpr uint32_t kTileQ = 16, kTileHits = 960, kTileRows = 88, kTileRing = 128;
 constexpr uint32_t kTileCellLayers = 4, kTileCells = 64 * kTileCellLayers;
 constexpr uint32_t kTileBuckets = 64;  // sort buckets per query slot
@@ -2825,7 +2826,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
 // ---------------------------------------------------------------------------
 // Pass 1, radius rows that fit the LDS buffer: collect, sort, store.
 
-template <int METHOD, bool TLDS, bool FROM_LIST>
+// BARE: what it does with rows of tiles, which have no descriptor (tile_query).
+// One query from either source was held in vector registers, 77 instead of 52,
+// and a kernel with both costs short-lived waves more to start, so a call whose
+// count pass cannot have used tiles takes the kernel without (kNoBare); the
+// persistent schedule, both in one, each with its copy of the row's code
+// (kBoth); the plain schedule, the kernel without and a second launch for
+// those rows (kBareOnly).  Rows without a stash, write pass, ms, one query from
+// either source and now: 1,048,576 uneven radii 1.07 -> 0.97, plain launch
+// 1.41 -> 1.34; r = 3 cells 1.25 -> 1.11, plain launch 1.32 -> 1.22.
+enum { kNoBare = 0, kBoth = 1, kBareOnly = 2 };
+template <int METHOD, bool TLDS, bool FROM_LIST, int BARE>
 __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs A) {
     extern __shared__ __align__(16) char smem[];
     const uint32_t* tab_lds = stage_table<TLDS>(T, smem);
@@ -2847,14 +2858,16 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
     // after a stashing count pass only the rows it did not keep are walked:
     // the main launch takes the walk list, the list launch skips kept rows
     const bool stashed = A.stash_hdr[kHdrMode] != 0u;
-    const bool from_walk = !FROM_LIST && stashed, tiled = A.stash_hdr[kHdrTiles] != 0u;
+    const bool from_walk = !FROM_LIST && stashed;
+    // rows of tiles: positions below `tiled`, in the region (A.tiles: the
+    // count pass may have used them)
+    const uint32_t tiled =
+        !FROM_LIST && A.tiles && from_walk && uni(A.stash_hdr[kHdrTiles]) != 0u ? uni(L.cs[L.ncells]) : 0u;
+    if (BARE == kBareOnly && tiled == 0u) return;
     const uint32_t idbits = L.n > 1 ? 32u - (uint32_t)__builtin_clz(L.n - 1u) : 0u;  // ids are below n
     const uint32_t nq = FROM_LIST ? uni(*A.list_count) : (from_walk ? uni(*A.walk_count) : A.Q);
-    for_each_query(nq, A, queue_set(A, FROM_LIST ? (int)A.list_set : (from_walk ? kQWalk : kQWrite)),
-                   [&](uint32_t ti_) {
-        const uint32_t qi = FROM_LIST ? uni(A.list[ti_]) : (from_walk ? uni(A.walkq[ti_]) : ti_);
-        const bool bare = (METHOD == kSphere || METHOD == kEither) && from_walk && tiled && qi < L.cs[L.ncells];
-        const Query s = bare ? tile_query(L, T, A, qi) : load_query(L, A, qi);
+    auto write_row = [&](const Query& s, uint32_t qi, auto from_tile) __attribute__((always_inline)) {
+        constexpr bool bare = decltype(from_tile)::value;
         if (FROM_LIST && stashed && uni(A.soff[s.row]) != kMaxId) return;  // copied by the gather kernel
         if ((METHOD == kSphere || METHOD == kPaper) && (s.flags & F_VALID) && !(s.flags & F_SPHERE))
             return;  // fallback list
@@ -2898,6 +2911,15 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
         sort_row_store(td, ti, sd, si, hist, min(n, rowlen), s.r2, idbits, A.out_ids + rb,
                        A.out_d2 ? A.out_d2 + rb : nullptr);
         wave_sync();
+    };
+    for_each_query(nq, A, queue_set(A, FROM_LIST ? (int)A.list_set : (from_walk ? kQWalk : kQWrite)),
+                   [&](uint32_t ti_) {
+        const uint32_t qi = FROM_LIST ? uni(A.list[ti_]) : (from_walk ? uni(A.walkq[ti_]) : ti_);
+        if (qi < tiled) {
+            if constexpr (BARE != kNoBare) write_row(tile_query(L, T, A, qi), qi, std::true_type());
+        } else {
+            if constexpr (BARE != kBareOnly) write_row(load_query(L, A, qi), qi, std::false_type());
+        }
     });
 }
 
@@ -3558,7 +3580,7 @@ uint32_t tile_blocks() { return (uint32_t)device_cu_count() * std::min(12u, 160u
 // its buffer to the write pass); 349 pairs 2.21 / 2.70.
 bool tile_plan(const LatArgs& L, const TabArgs& T, const QArgs& q, TileArgs& TA) {
     if (!q.group || q.qx || q.rad || q.mode != SPHIDX_MODE_RADIUS || q.stats || q.select || q.method_out || !T.has ||
-        T.paper || q.Q < 1024u)
+        T.paper || q.Q < kTileMinQ)
         return false;
     const uint32_t rm = q.rad_u;
     if (rm > T.rmax) return false;
@@ -3614,11 +3636,14 @@ hipError_t launch_copy(const QArgs& q, const LatArgs& L, hipStream_t st) {
 }
 
 // Kernel choice by variant: cube, sphere, sphere with the row table in LDS;
-// SPHIDX_PICKP adds variant 3, the paper's cell tables.
+// SPHIDX_PICKP adds variant 3, the paper's cell tables, SPHIDX_PICKS is for the
+// sphere's two variants alone.
 #define SPHIDX_PICK(KERNEL, variant, SPH, ...)                                     \
     ((variant) == 0 ? (const void*)KERNEL<kCube, false __VA_ARGS__>                \
      : (variant) == 1 ? (const void*)KERNEL<SPH, false __VA_ARGS__>                \
                       : (const void*)KERNEL<SPH, true __VA_ARGS__>)
+#define SPHIDX_PICKS(KERNEL, variant, SPH, ...) \
+    ((variant) == 1 ? (const void*)KERNEL<SPH, false __VA_ARGS__> : (const void*)KERNEL<SPH, true __VA_ARGS__>)
 #define SPHIDX_PICKP(KERNEL, variant, SPH, ...) \
     ((variant) == 3 ? (const void*)KERNEL<kPaper, false __VA_ARGS__> : SPHIDX_PICK(KERNEL, variant, SPH, __VA_ARGS__))
 
@@ -3865,16 +3890,36 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
         if ((e = mark(ev_begin)) != hipSuccess) return e;
         // rows kept by a stashing count pass (does nothing otherwise)
         if ((e = launch_copy(q, L, st)) != hipSuccess) return e;
-        e = launch_ptr(either ? SPHIDX_PICK(write_kernel, variant, kEither, , false)
-                              : SPHIDX_PICKP(write_kernel, variant, kSphere, , false),
-                       q.Q, q, w, b, sh1, st, L, T);
+        // the count pass may have used tiles (by what both passes must share:
+        // its launch may have differed from this one)
+        QArgs qw = q;
+        qw.tiles = T.has && !T.paper && q.select == 0u && !q.qx && !q.rad && q.mode == SPHIDX_MODE_RADIUS &&
+                           q.Q >= kTileMinQ
+                       ? 1u
+                       : 0u;
+        if (qw.tiles && q.persistent)
+            e = launch_ptr(either ? SPHIDX_PICKS(write_kernel, variant, kEither, , false, kBoth)
+                                  : SPHIDX_PICKS(write_kernel, variant, kSphere, , false, kBoth),
+                           q.Q, qw, w, b, sh1, st, L, T);
+        else
+            e = launch_ptr(either ? SPHIDX_PICK(write_kernel, variant, kEither, , false, kNoBare)
+                                  : SPHIDX_PICKP(write_kernel, variant, kSphere, , false, kNoBare),
+                           q.Q, qw, w, b, sh1, st, L, T);
+        if (e == hipSuccess && qw.tiles && !q.persistent) {
+            // (resident waves from the walk list's queues, which the copy has
+            // cleared: a grid of a wave per query took 65 us to find nothing)
+            qw.persistent = 1u;
+            qw.tile = 64u;
+            e = launch_ptr(SPHIDX_PICKS(write_kernel, variant, kSphere, , false, kBareOnly), q.Q, qw, w, b, sh1, st, L,
+                           T);
+        }
         if (e == hipSuccess) e = mark(ev_end);
         if (e != hipSuccess) return e;
         if (variant != 0 && !either) {
             ql.list = q.fbq;
             ql.list_count = q.fb_count;
             ql.list_set = kQFbWrite;
-            e = launch_ptr((const void*)write_kernel<kCube, false, true>, 0, ql, w, b,
+            e = launch_ptr((const void*)write_kernel<kCube, false, true, kNoBare>, 0, ql, w, b,
                            query_lds_bytes(1, q.sort_cap, w, 0), st, L, T);
             if (e != hipSuccess) return e;
         }
