@@ -2295,20 +2295,6 @@ __device__ __forceinline__ void swap_rows16(double& a, double& b) {
     b = __hiloint2double((int)bh, (int)bl);
 }
 
-// v plus this lane's bit of a wave mask (one add with the mask as carry).
-__device__ __forceinline__ uint32_t add_bit(uint32_t v, uint64_t m) {
-    uint32_t r;
-    uint64_t carry;
-    asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(r), "=s"(carry) : "v"(v), "s"(m));
-    return r;
-}
-
-__device__ __forceinline__ uint32_t sub_bit(uint32_t v, uint64_t m) {
-    uint32_t r;
-    uint64_t borrow;
-    asm("v_subb_co_u32 %0, %1, %2, 0, %3" : "=v"(r), "=s"(borrow) : "v"(v), "s"(m));
-    return r;
-}
 // The next lane's value (lane 63: all ones).
 __device__ __forceinline__ uint64_t next_lane(uint64_t v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)(uint32_t)v, 0x130, 0xF, 0xF, false);
@@ -2472,32 +2458,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
                     swap_rows16(id[0], id[1]);
                     swap_rows16(id[2], id[3]);
                     dbl4 D[4];
-                    uint64_t H[16];
+                    bool H[16];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) D[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, b[j], C, 0, 0, 0);
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            H[4 * j + i] = __ballot(D[j][i] <= thr[i]);
-                            if (EXCL) H[4 * j + i] &= __ballot(id[j] != selfp[i]);
+                            H[4 * j + i] = D[j][i] <= thr[i];
+                            if (EXCL) H[4 * j + i] = H[4 * j + i] && id[j] != selfp[i];
                         }
                     if (!STASH) {
 #pragma unroll
-                        for (int j = 0; j < 16; ++j) cnt[j & 3] = add_bit(cnt[j & 3], H[j]);
+                        for (int j = 0; j < 16; ++j) cnt[j & 3] += H[j] ? 1u : 0u;
                     } else {
                         // every lane writes its own hits, from its place in the
                         // prefix of their numbers (past the buffer: counted only)
                         uint32_t mc = 0;
 #pragma unroll
-                        for (int j = 0; j < 16; ++j) mc = add_bit(mc, H[j]);
+                        for (int j = 0; j < 16; ++j) mc += H[j] ? 1u : 0u;
                         const uint32_t incl = scan_add(mc);
                         const uint32_t n = lane_val(incl, 63);
                         uint64_t* w = hb + (hcount + incl - mc);
                         if (hcount + n <= kTileHits) {
 #pragma unroll
                             for (int j = 0; j < 16; ++j)
-                                if (__builtin_expect(lane_in(H[j]), 1)) {
+                                if (__builtin_expect(H[j], 1)) {
                                     *w = ((uint64_t)__double_as_longlong(D[j >> 2][j & 3]) << sh) | id[j >> 2];
                                     ++w;
                                 }
@@ -2772,18 +2758,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
 #pragma unroll
                         for (uint32_t k = 0; k < kTileNear; ++k)
                             if (k + 1u < near) next[k] = next_lane(key[k]);
+                        // (one add or subtract with the comparison's mask as
+                        // carry each; plain code, as the compiler keeps the wait
+                        // states between the two, which it does not for inline
+                        // assembly.  Leaving the loop by a break keeps it
+                        // rolled, the keys in indexed registers: the 8.4
+                        // M-agent timestep 7.65 ms instead of 5.11)
 #pragma unroll
                         for (uint32_t d = 1; d <= kTileNear; ++d) {
-                            if (d >= near) break;
+                            if (d < near)
 #pragma unroll
                             for (uint32_t k = 0; k < kTileSteps; ++k) {
                                 const bool in = k + d < kTileSteps;
-                                const uint64_t m = __ballot((in ? key[k + d] : next[k + d - kTileSteps]) < key[k]);
-                                rk[k] = add_bit(rk[k], m);
+                                const bool less = (in ? key[k + d] : next[k + d - kTileSteps]) < key[k];
+                                rk[k] += less ? 1u : 0u;
                                 if (in)
-                                    rk[k + d] = sub_bit(rk[k + d], m);
+                                    rk[k + d] -= less ? 1u : 0u;
                                 else
-                                    rk[k + d - kTileSteps] = sub_bit(rk[k + d - kTileSteps], m << 1);
+                                    rk[k + d - kTileSteps] -= lane_in(__ballot(less) << 1) ? 1u : 0u;
                             }
                         }
                         wave_sync();
