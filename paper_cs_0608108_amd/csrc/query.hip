@@ -1372,7 +1372,7 @@ constexpr int kQCount = 0, kQWrite = 1, kQTopm = 2, kQFbCount = 3, kQFbWrite = 4
 // the count pass's last list (rows the second grouped round left) takes the
 // fallback write set, which only the write pass uses and clears
 constexpr int kQExtra2 = kQFbWrite;
-// Longest radius row the block-per-row kernel orders in LDS (28 bytes per pair).
+// Longest radius row the block-per-row kernel orders in LDS (12 bytes per pair).
 constexpr uint32_t kLongCap = 3072;
 
 __device__ __forceinline__ uint32_t* queue_set(const QArgs& A, int set) {
@@ -3113,14 +3113,15 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
 }
 
 // ---------------------------------------------------------------------------
-// Pass 1, radius rows longer than a wavefront's LDS row buffer and at most
-// kLongCap pairs: one block of W waves per row.  Wave w walks the row's
-// table entries in 64-entry steps w, w + W, ..., tests their candidates and
-// appends its hits to a block-wide LDS buffer (one LDS atomic per wave
-// step).  The block then orders the row by (dist^2, id) with one bucket
-// sort -- bucket floor(n d^2 / r^2), capped at n - 1, is monotone in d^2 --
-// and an exact rank inside each bucket, and stores it.  Rows come from the
-// long-row list one per block; the top-M kernel leaves them alone.
+// Both passes, radius rows longer than a wavefront's LDS row buffer: one block
+// of W waves per row.  Wave w walks the row's table entries in 64-entry steps
+// w, w + W, ..., tests their candidates and appends its hits to a block-wide
+// LDS buffer (one LDS atomic per wave step).  The block then orders the row by
+// (dist^2, id) with one bucket sort (block_sort_store) and stores it; the
+// write pass orders a row past the buffer's kLongCap pairs by shells of
+// distance (shell_row).  The top-M kernel takes such rows only where many of
+// their objects lie at one distance (F_WINDOW), and all of them where one
+// wavefront per row is asked for.
 
 // Exclusive scan over the block of one value per thread; `wsum` holds one
 // word per wavefront.
@@ -3135,24 +3136,38 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum) 
     return off + incl - v;
 }
 
-// Order the block's n <= kLongCap keys (dist^2 - base) << idbits | id and store
-// them at dst; the distances are at most span above base.  One counting sort
-// over about n buckets (floor(n v / (v_max + 1)) of v = the top 24 bits of the
-// distance: monotone), the keys held in registers and put in place, then each
-// key's rank from its place and the keys near it (as the tile kernel's).
-// kb[-kNearPad .. n + kNearPad) is the block's.
+// Order the block's n <= kLongCap pairs by (dist^2, id) and store them at dst;
+// kb holds their distances above base, at most span.  One counting sort over
+// about n buckets (floor(n v / (v_max + 1)) of v = the top 24 bits of the
+// distance: monotone), the pairs held in registers and put in place, then each
+// one's rank from its place and the pairs near it (as the tile kernel's).
+// A pair is one key, distance << idbits | id, and `side` holds the bucket
+// counts; WIDE, where a distance leaves no room for an id: kb holds the
+// distances, `side` the ids, and the counts take kb's place while the pairs are
+// in registers (three barriers more, the same LDS).  kb[-kNearPad .. n + kNearPad)
+// is the block's.
 constexpr uint32_t kNearPad = 8;
 
-template <int W>
-__device__ void block_sort_store(uint64_t* kb, uint32_t* hist, uint32_t* ctl, uint32_t n, uint64_t span,
+template <int W, bool WIDE>
+__device__ void block_sort_store(uint64_t* kb, uint32_t* side, uint32_t* ctl, uint32_t n, uint64_t span,
                                  uint32_t idbits, uint32_t* dst_ids, int64_t* dst_d2, uint64_t base = 0) {
     constexpr uint32_t nt = 64u * W, kPer = kLongCap / nt;
     const uint32_t tid = threadIdx.x;
     const uint32_t sbits = span ? 64u - (uint32_t)__builtin_clzll(span) : 0u;
-    const uint32_t vs = min(sbits > 24u ? sbits - 24u : 0u, 63u - idbits);
+    const uint32_t low = WIDE ? 0u : idbits;
+    const uint32_t vs = min(sbits > 24u ? sbits - 24u : 0u, 63u - low);
     const float scale = (float)n / ((float)(span >> vs) + 1.0f);
+    uint32_t* hist = WIDE ? (uint32_t*)kb : side;
     uint64_t key[kPer];
     uint32_t bs[kPer];  // bucket | place in bucket << 16
+    if (WIDE) {
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) {
+            const uint32_t t = tid + k * nt;
+            if (k * nt < n && t < n) key[k] = kb[t];
+        }
+        __syncthreads();
+    }
     for (uint32_t t = tid; t < n; t += nt) hist[t] = 0u;
     if (tid == 0) ctl[3] = 0u;
     __syncthreads();
@@ -3160,8 +3175,8 @@ __device__ void block_sort_store(uint64_t* kb, uint32_t* hist, uint32_t* ctl, ui
     for (uint32_t k = 0; k < kPer; ++k) {
         const uint32_t t = tid + k * nt;
         if (k * nt < n && t < n) {
-            key[k] = kb[t];
-            const uint32_t b = min((uint32_t)((float)(uint32_t)(key[k] >> (idbits + vs)) * scale), n - 1u);
+            if (!WIDE) key[k] = kb[t];
+            const uint32_t b = min((uint32_t)((float)(uint32_t)(key[k] >> (low + vs)) * scale), n - 1u);
             bs[k] = b | (atomicAdd(&hist[b], 1u) << 16);
         }
     }
@@ -3186,21 +3201,44 @@ __device__ void block_sort_store(uint64_t* kb, uint32_t* hist, uint32_t* ctl, ui
             }
     }
     __syncthreads();
+    if (WIDE) {
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k)
+            if (k * nt < n && tid + k * nt < n) bs[k] = hist[bs[k] & 0xFFFFu] + (bs[k] >> 16);
+        __syncthreads();
+    }
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k)
-        if (k * nt < n && tid + k * nt < n) kb[hist[bs[k] & 0xFFFFu] + (bs[k] >> 16)] = key[k];
-    if (tid < kNearPad) {
+        if (k * nt < n && tid + k * nt < n) {
+            const uint32_t to = WIDE ? bs[k] : hist[bs[k] & 0xFFFFu] + (bs[k] >> 16);
+            kb[to] = key[k];
+            // (the ids follow, in the keys' registers)
+            if (WIDE) key[k] = side[tid + k * nt];
+        }
+    if (WIDE) {
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k)
+            if (k * nt < n && tid + k * nt < n) side[bs[k]] = (uint32_t)key[k];
+    }
+    if (!WIDE && tid < kNearPad) {
         // nothing before the first key is larger, nothing after the last smaller
         kb[(int)tid - (int)kNearPad] = 0ull;
         kb[n + tid] = ~0ull;
     }
     __syncthreads();
-    const uint32_t near = ctl[3];  // keys of the fullest bucket
+    const uint32_t near = ctl[3];  // pairs of the fullest bucket
     const uint64_t idm = (1ull << idbits) - 1ull;
     for (uint32_t t = tid; t < n; t += nt) {
         const uint64_t kv = kb[t];
+        const uint32_t iv = WIDE ? side[t] : (uint32_t)(kv & idm);
         uint32_t rk = t;
-        if (near <= kNearPad + 1u) {
+        if (WIDE) {
+            for (uint32_t d = 1; d < near; ++d) {
+                if (t + d < n && key_less(kb[t + d], side[t + d], kv, iv)) ++rk;
+                if (d <= t && key_less(kv, iv, kb[t - d], side[t - d])) --rk;
+            }
+        } else if (near <= kNearPad + 1u) {
             for (int d = 1; d < (int)near; ++d)
                 rk += (kb[(int)t + d] < kv ? 1u : 0u) - (kb[(int)t - d] > kv ? 1u : 0u);
         } else {
@@ -3209,38 +3247,53 @@ __device__ void block_sort_store(uint64_t* kb, uint32_t* hist, uint32_t* ctl, ui
                 if (d <= t && kb[t - d] > kv) --rk;
             }
         }
-        dst_ids[rk] = (uint32_t)(kv & idm);
-        if (dst_d2) dst_d2[rk] = (int64_t)((kv >> idbits) + base);
+        dst_ids[rk] = iv;
+        if (dst_d2) dst_d2[rk] = (int64_t)((kv >> low) + base);
     }
 }
 
-// A radius row of more than kLongCap pairs (or whose keys do not pack), by one
-// block in two walks (write pass): the first counts its hits per distance bucket (dist^2 >> sh, sh such
+// A radius row of more than kLongCap pairs, by one block in two walks (write
+// pass): the first counts its hits per distance bucket (dist^2 >> sh, sh such
 // that r^2 falls below kShellBuckets), the second writes each hit's sorted
 // position into the row's own output, grouped by bucket; then runs of buckets
 // of at most kShellCap pairs (shells, centre to edge) are read back into LDS,
 // their objects' distances computed again, ordered by the block sort and
 // stored in place.  The row needs no memory but its output.  Returns false,
 // with nothing written, when one bucket alone holds more than kShellCap pairs
-// (many objects at one distance) or spans more distances than pack with an id:
-// such a row is left to the windowed kernel.
+// (many objects at one distance): such a row is left to the windowed kernel.
 // What bounds it is the walk's and the block sort's instruction issue and LDS
 // traffic.  Before, every such row took one window of sort_cap pairs after
 // another on one wavefront, each window walking the whole row again: 512 rows
 // of about 20,000 pairs (20 objects per cell, 7 cells, clipped 32^3) took
 // 103 ms in all; now 0.65 ms.
+// Keys (block_sort_store) hold a shell's distances from its first bucket's on,
+// so they pack far beyond a whole row's; WIDE where so few buckets pack that
+// shells would be cut by them and not by their pairs (shells_wide): 512 rows of
+// 12,500 pairs at r = 32 cells, 256 buckets to a key, 0.56 ms, wide 0.60.
 constexpr uint32_t kShellCap = 2304, kShellBuckets = 2048;
 
-template <int METHOD, int W>
+// log2 of the distances per bucket.
+__device__ __forceinline__ uint32_t shell_shift(uint64_t r2) {
+    const uint32_t rbits = r2 ? 64u - (uint32_t)__builtin_clzll(r2) : 0u;
+    return rbits > 11u ? rbits - 11u : 0u;  // kShellBuckets = 2^11
+}
+// Buckets whose distances, from the first's on, pack with an id (0: not one's).
+__device__ __forceinline__ uint32_t shell_buckets(uint64_t r2, uint32_t idbits) {
+    const uint32_t used = shell_shift(r2) + idbits;
+    return used > 64u ? 0u : 64u - used >= 11u ? kShellBuckets : 1u << (64u - used);
+}
+__device__ __forceinline__ bool shells_wide(uint64_t r2, uint32_t idbits, uint32_t rowlen) {
+    const uint32_t b = shell_buckets(r2, idbits);
+    return b == 0u || (b < kShellBuckets && (uint64_t)(kShellBuckets / b) * kShellCap > 2ull * rowlen);
+}
+
+template <int METHOD, int W, bool WIDE>
 __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, const AxisWrap& aw, const Query& s,
-                          int64_t rb, uint32_t rowlen, uint32_t idbits, uint64_t* kb, uint32_t* hist, uint32_t* bkt,
+                          int64_t rb, uint32_t rowlen, uint32_t idbits, uint64_t* kb, uint32_t* side, uint32_t* bkt,
                           uint32_t* own, uint32_t* ctl) {
     const uint32_t tid = threadIdx.x, nt = blockDim.x, wave = tid >> 6, nw = nt >> 6;
-    const uint32_t rbits = s.r2 ? 64u - (uint32_t)__builtin_clzll(s.r2) : 0u;
-    const uint32_t sh = rbits > 11u ? rbits - 11u : 0u;  // kShellBuckets = 2^11
-    if (sh + idbits > 64u) return false;  // a bucket's distances do not pack with an id
-    // buckets whose distances, from the first's on, do
-    const uint32_t most_b = 64u - idbits - sh >= 11u ? kShellBuckets : 1u << (64u - idbits - sh);
+    const uint32_t sh = shell_shift(s.r2);
+    const uint32_t most_b = WIDE ? kShellBuckets : shell_buckets(s.r2, idbits);
     uint32_t cand = 0, walked = 0;
     auto walk_row = [&](auto&& visit) {
         walk<METHOD, false, false>(L, T, nullptr, s, false, walked, [&]() { return s.r2; },
@@ -3302,12 +3355,14 @@ __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, co
         const uint64_t span = min(s.r2, ((uint64_t)e << sh) - 1ull) - base;
         for (uint32_t t = tid; t < n; t += nt) {
             const uint4 P = L.pts[pos[t0 + t]];
-            kb[t] = ((obj_dist2(aw, s, P) - base) << idbits) | P.w;
+            const uint64_t d2 = obj_dist2(aw, s, P) - base;
+            kb[t] = WIDE ? d2 : (d2 << idbits) | P.w;
+            if (WIDE) side[t] = P.w;
         }
         __syncthreads();
         if (n > 0)
-            block_sort_store<W>(kb, hist, ctl, n, span, idbits, A.out_ids + rb + t0,
-                                A.out_d2 ? A.out_d2 + rb + t0 : nullptr, base);
+            block_sort_store<W, WIDE>(kb, side, ctl, n, span, idbits, A.out_ids + rb + t0,
+                                      A.out_d2 ? A.out_d2 + rb + t0 : nullptr, base);
         __syncthreads();
         t0 += n;
         b = e;
@@ -3322,19 +3377,25 @@ __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, co
 // the stash (one allocation per row) for the write pass to copy; otherwise
 // the row goes on the big or the walk list like any row the count pass did not
 // keep.  The write pass's form takes the big list and the long-row list.
-// A row's hits are kept as keys dist^2 << idbits | id; one whose distances do
-// not leave room for an id is counted only, and ordered by shells.
+// A row's hits are kept as keys dist^2 << idbits | id, or, where r^2 leaves no
+// room for an id in 64 bits (16 fractional bits: past r = 16 cells at 16.7 M
+// objects), as distances with the ids beside them, in the same LDS: counted
+// only, and walked thrice more by the write pass, 8,192 such rows of about
+// 3,100 pairs (16.7 M objects, r = 20 cells) took 2.18 ms and of 2,090 (33 M,
+// r = 14) 1.27 ms; kept, 1.47 and 0.48 ms.
 // A row is a chain of barriers with little work between them, so rows in flight
 // are what counts: 12 bytes of LDS per pair (keys, bucket counts) let four
 // blocks share a CU, where pairs with an index each, 20 bytes, let two: 16,400
 // rows of about 1,100 pairs (a service's batch of 65,536) took 528 us.
+// (Registers for the blocks that the LDS leaves room for: four per CU are W
+// wavefronts per SIMD.)
 template <int METHOD, bool COUNT, int W>
-__global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArgs A) {
+__global__ __launch_bounds__(64 * W, COUNT || W < 8 ? W : 6) void long_kernel(LatArgs L, TabArgs T, QArgs A) {
     extern __shared__ __align__(16) char smem[];
     uint64_t* kb = (uint64_t*)smem + kNearPad;        // hits in arrival order
-    uint32_t* hist = (uint32_t*)(kb + kLongCap + kNearPad);
-    uint32_t* ctl = hist + kLongCap;  // [0] hits so far, [1] list entry taken, [2] stash offset, [3] fullest bucket,
-                                      // [4, 12) wave sums, [12] keys that do not pack
+    uint32_t* side = (uint32_t*)(kb + kLongCap + kNearPad);  // bucket counts, or the hits' ids
+    uint32_t* ctl = side + kLongCap;  // [0] hits so far, [1] list entry taken, [2] stash offset, [3] fullest bucket,
+                                      // [4, 12) wave sums
     const uint32_t wave = threadIdx.x >> 6, nw = W, lane = lane_id();
     uint32_t* own = ctl + 16 + wave * 64;
     static_assert(kShellCap * 12 + kShellBuckets * 4 <= kLongCap * 12, "a shell's buffers fit the row's");
@@ -3349,7 +3410,7 @@ __global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArg
     for (;;) {
         if (threadIdx.x == 0) {
             ctl[1] = atomicAdd(qc, 1u);
-            ctl[0] = ctl[12] = 0u;
+            ctl[0] = 0u;
         }
         __syncthreads();
         const uint32_t t = uni(ctl[1]);
@@ -3364,6 +3425,7 @@ __global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArg
         }
         // the same for every wave of the block
         const bool mine = (s.flags & F_VALID) && !(s.flags & (F_KNN | F_WINDOW)) && rowlen > 0;
+        const bool wide = (s.r2 >> (64u - idbits)) != 0;
         if (mine && rowlen <= kLongCap) {
             uint32_t cand = 0, walked = 0;
             auto visit = [&](bool act, uint32_t p, const uint4& P) -> bool {
@@ -3376,8 +3438,8 @@ __global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArg
                     base = uni(base);
                     const uint32_t slot = lanes_below(hm, base);
                     if (hit && slot < kLongCap) {
-                        kb[slot] = (d2 << idbits) | P.w;
-                        if (d2 >> (64u - idbits)) ctl[12] = 1u;
+                        kb[slot] = wide ? d2 : (d2 << idbits) | P.w;
+                        if (wide) side[slot] = P.w;
                     }
                 }
                 return false;
@@ -3388,7 +3450,6 @@ __global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArg
             }, 64u * wave, 64u * nw);
         }
         __syncthreads();
-        const bool packs = ctl[12] == 0u;
         if (COUNT) {
             const uint32_t n = (s.flags & F_VALID) ? ctl[0] : 0u;
             if (threadIdx.x == 0) {
@@ -3396,7 +3457,7 @@ __global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArg
                 uint32_t off = 0u;  // empty rows: nothing to copy
                 if (n > 0) {
                     off = kMaxId;
-                    if (n <= kLongCap && packs && A.stash) {
+                    if (n <= kLongCap && A.stash) {
                         const uint32_t c = atomicAdd(A.stash_ctr + region * SPHIDX_QSTRIDE, n);
                         if ((uint64_t)c + n <= A.stash_region) off = region * A.stash_region + c;
                     }
@@ -3407,17 +3468,29 @@ __global__ __launch_bounds__(64 * W) void long_kernel(LatArgs L, TabArgs T, QArg
             }
             __syncthreads();
             const uint32_t off = ctl[2];
-            if (n > 0 && off != kMaxId)
-                block_sort_store<W>(kb, hist, ctl, n, s.r2, idbits, A.stash_ids + off,
-                                    A.stash_d2 ? A.stash_d2 + off : nullptr);
+            if (n > 0 && off != kMaxId) {
+                int64_t* d2 = A.stash_d2 ? A.stash_d2 + off : nullptr;
+                if (wide)
+                    block_sort_store<W, true>(kb, side, ctl, n, s.r2, idbits, A.stash_ids + off, d2);
+                else
+                    block_sort_store<W, false>(kb, side, ctl, n, s.r2, idbits, A.stash_ids + off, d2);
+            }
         } else if (mine) {
-            if (rowlen <= kLongCap && packs) {
-                block_sort_store<W>(kb, hist, ctl, min(ctl[0], rowlen), s.r2, idbits, A.out_ids + rb,
-                                    A.out_d2 ? A.out_d2 + rb : nullptr);
+            if (rowlen <= kLongCap) {
+                const uint32_t n = min(ctl[0], rowlen);
+                int64_t* d2 = A.out_d2 ? A.out_d2 + rb : nullptr;
+                if (wide)
+                    block_sort_store<W, true>(kb, side, ctl, n, s.r2, idbits, A.out_ids + rb, d2);
+                else
+                    block_sort_store<W, false>(kb, side, ctl, n, s.r2, idbits, A.out_ids + rb, d2);
             } else {
                 uint32_t* bkt = (uint32_t*)(kb + kShellCap + kNearPad);
-                if (!shell_row<METHOD, W>(L, T, A, aw, s, rb, rowlen, idbits, kb, bkt + kShellBuckets, bkt, own, ctl) &&
-                    threadIdx.x == 0)
+                uint32_t* sd = bkt + kShellBuckets;
+                const bool done =
+                    shells_wide(s.r2, idbits, rowlen)
+                        ? shell_row<METHOD, W, true>(L, T, A, aw, s, rb, rowlen, idbits, kb, sd, bkt, own, ctl)
+                        : shell_row<METHOD, W, false>(L, T, A, aw, s, rb, rowlen, idbits, kb, sd, bkt, own, ctl);
+                if (!done && threadIdx.x == 0)
                     ((uint32_t*)(A.desc + 4 * (size_t)qi))[6] = s.flags | F_WINDOW;
             }
         }
@@ -3916,8 +3989,8 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
             if (e != hipSuccess) return e;
         }
         // K-NN rows of a mixed batch and long radius rows, from the list:
-        // radius rows up to kLongCap pairs one block per row, the others
-        // one wavefront per row (windowed top-M)
+        // radius rows one block per row, the others (and radius rows whose
+        // pairs crowd at one distance) one wavefront per row
         ql.list = q.longq;
         ql.list_count = q.long_count;
         if (q.long_waves > 1) {
