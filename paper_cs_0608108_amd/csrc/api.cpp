@@ -292,10 +292,8 @@ void plan_stash(QArgs& A, const sphidx_csr* csr, const Launch& ln, bool interior
     A.stash_region = (uint32_t)region;
     A.stash_ids = (uint32_t*)A.stash_base;
     A.stash_d2 = d2 ? (int64_t*)(A.stash_base + align_up(region * SPHIDX_NREGION * 4)) : nullptr;
-    // about 8 grabs per resident wave and region: little tail left unused
-    const uint64_t waves = (uint64_t)device_cu_count() * ln.bpc * ln.waves;
-    const uint64_t per = std::max<uint64_t>(1, waves / SPHIDX_NREGION);
-    A.stash_chunk = (uint32_t)std::min<uint64_t>(8192, std::max<uint64_t>(ln.cap, region / (per * 8)));
+    // (the tile kernel's wavefronts are its own: launch_query_pass)
+    A.stash_chunk = stash_chunk(A.stash_region, (uint64_t)device_cu_count() * ln.bpc * ln.waves, ln.cap);
 }
 
 // Whether the count pass takes a batch in groups when the launch leaves it to

@@ -2703,24 +2703,34 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
                 // the stash
                 const bool write = lane < n0;
                 if (write) A.row_ptr[row] = (int64_t)nq;
-                bool ok = fits;
-                if (ok && total > 0 && cur + total > lim) {
-                    ok = false;
+                // the first `split` pairs, rows that end inside the wave's
+                // chunk, go there, the rest to a new one: a group's pairs are
+                // often as many as a chunk holds, and dropping what is left of
+                // it would leave a stash of the size that keeps every row half
+                // empty (1,048,576 agents in 128^3, count and write: r = 2.5
+                // 0.625 -> 0.500 ms, r = 3 0.75 -> 0.69)
+                uint32_t split = total, next_at = 0, kept = fits ? total : 0u;
+                if (kept > 0 && cur + total > lim) {
+                    const uint32_t end = qs0 + nq;
+                    split = lane_val(scan_max(slot < n0 && end <= lim - cur ? end : 0u), 63);
+                    kept = split;
                     if (!dry) {
-                        const uint32_t grab = max(A.stash_chunk, total);
+                        const uint32_t grab = max(A.stash_chunk, total - split);
                         uint32_t t = 0;
                         if (lane == 0) t = atomicAdd(A.stash_ctr + region * SPHIDX_QSTRIDE, grab);
                         t = uni(t);
                         if ((uint64_t)t + grab <= A.stash_region) {
-                            cur = region * A.stash_region + t;
-                            lim = cur + grab;
-                            ok = true;
+                            next_at = region * A.stash_region + t;
+                            lim = next_at + grab;
+                            kept = total;
                         } else {
                             dry = true;
                         }
                     }
                 }
-                if (ok && total > 0) {
+                auto place = [&](uint32_t t) -> uint32_t { return t < split ? cur + t : next_at + (t - split); };
+                const bool keep = nq > 0 && qs0 + nq <= kept;
+                if (kept > 0) {
                     // keys to their buckets; the keys are all in registers, so
                     // the buffer is written in place
 #pragma unroll
@@ -2782,10 +2792,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
 #pragma unroll
                         for (uint32_t k = 0; k < kTileSteps; ++k) hb[rk[k]] = key[k];
                         wave_sync();
-                        for (uint32_t t = lane; t < total; t += 64) {
+                        for (uint32_t t = lane; t < kept; t += 64) {
                             const uint64_t kv = hb[t];
-                            A.stash_ids[cur + t] = (uint32_t)kv & idm;
-                            if (A.stash_d2) A.stash_d2[cur + t] = (int64_t)((kv << 4) >> (64u - d2b));
+                            const uint32_t at = place(t);
+                            A.stash_ids[at] = (uint32_t)kv & idm;
+                            if (A.stash_d2) A.stash_d2[at] = (int64_t)((kv << 4) >> (64u - d2b));
                         }
                     } else {
                         for (uint32_t t = lane; t < total; t += 64) {
@@ -2795,19 +2806,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
                                 if (t + d < total && hb[t + d] < kv) ++rk;
                                 if (d <= t && hb[t - d] > kv) --rk;
                             }
-                            A.stash_ids[cur + rk] = (uint32_t)kv & idm;
-                            if (A.stash_d2) A.stash_d2[cur + rk] = (int64_t)((kv << 4) >> (64u - d2b));
+                            if (rk >= kept) continue;
+                            const uint32_t at = place(rk);
+                            A.stash_ids[at] = (uint32_t)kv & idm;
+                            if (A.stash_d2) A.stash_d2[at] = (int64_t)((kv << 4) >> (64u - d2b));
                         }
                     }
-                    if (write) A.soff[row] = cur + qs0;
-                    cur += total;
-                } else {
-                    // not kept: the write pass walks these rows again
-                    const bool walk_again = write && nq > 0;
-                    if (write) A.soff[row] = walk_again ? kMaxId : 0u;
-                    // (no descriptor yet: the write kernel makes it and passes a long row on)
-                    if (walk_again) list_row_again(A, qpos, false);
                 }
+                // rows not kept are walked again by the write pass (no
+                // descriptor yet: the write kernel makes it and passes a long
+                // row on)
+                if (write) A.soff[row] = keep ? place(qs0) : nq > 0 ? kMaxId : 0u;
+                if (write && nq > 0 && !keep) list_row_again(A, qpos, false);
+                cur = kept > split ? next_at + (total - split) : cur + min(split, kept);
                 wave_sync();
                 Q = Qn;
             }
@@ -3781,6 +3792,7 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
     // rows kept by the tile kernel need no descriptor (without the stash the
     // write pass walks every row)
     q.tiles = tiles && q.stash ? 1u : 0u;
+    if (q.tiles) q.stash_chunk = stash_chunk(q.stash_region, tile_blocks(), q.sort_cap);
     q.merged = !tiles && T.has && !T.paper && q.select == 0u && q.Q <= kMergedQ ? 1u : 0u;
     // optional timing events around the pass's main kernel(s)
     auto mark = [st](hipEvent_t ev) { return ev ? hipEventRecord(ev, st) : hipSuccess; };

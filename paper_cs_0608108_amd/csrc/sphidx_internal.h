@@ -187,6 +187,14 @@ enum : uint32_t { kHdrMode = 0, kHdrElems = 1, kHdrHasD2 = 2, kHdrD2Off = 3, kHd
 #define SPHIDX_MAX_LOG2_SUM 30
 static_assert(SPHIDX_NQUEUE <= 64 && SPHIDX_NQUEUE % SPHIDX_NXCD == 0, "a wave looks at every queue at once");
 
+// Stash elements per allocation grab of a count pass of `waves` wavefronts:
+// about 8 grabs per wavefront and region, so that little tail is left unused.
+inline uint32_t stash_chunk(uint32_t region, uint64_t waves, uint32_t cap) {
+    const uint64_t per = waves / SPHIDX_NREGION > 1 ? waves / SPHIDX_NREGION : 1;
+    const uint64_t c = region / (per * 8);
+    return c > 8192 ? 8192u : c < cap ? cap : (uint32_t)c;
+}
+
 constexpr uint32_t kPaperMaxOff = 32;
 
 // LDS bytes of the staged row table: the whole table, or the first
