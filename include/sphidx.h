@@ -331,8 +331,10 @@ typedef struct {
                             wavefront; the stash needs K pairs per such row);
                             0: the library's choice: groups for all-agents batches of the
                             sphere method from 16,384 queries on whose expected rows fit
-                            the buffer (K-NN: K <= 64 and rows kept), else one query per
-                            wavefront (always with per-query statistics) */
+                            the buffer (K-NN: rows kept, and one K of at most 64 or a K per
+                            query, of which those past sort_cap / 2 are searched one per
+                            wavefront), else one query per wavefront (always with
+                            per-query statistics) */
     /* METHOD_AUTO (Appendix: weighting factor and reversal distances).  A radius query takes
      * the sphere when select_weight/256 * (sphere cells) <= (cube cells), else the cube; then
      * the non-empty list instead if it holds fewer cells than the one chosen (plain counts).

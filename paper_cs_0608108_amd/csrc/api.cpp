@@ -306,8 +306,11 @@ void plan_stash(QArgs& A, const sphidx_csr* csr, const Launch& ln, bool interior
 // 0.082; r = 3, 131 K 0.230 / 0.166; r = 4 (135 pairs) 0.342 / 0.331, 227 pairs
 // 1.87 / 1.97; uneven radii to 4 cells, 1 M 1.22 / 0.79; K = 10, 99 K 0.321 /
 // 0.260; K = 40 0.462 / 0.434; K = 16 in clusters, 262 K 0.718 / 0.288; without
-// the stash r = 3 0.309 / 0.261 but K = 10 0.366 / 0.524.  (Given centres are
-// left alone: a service's mixed batch took 1.39 / 1.56.)
+// the stash r = 3 0.309 / 0.261 but K = 10 0.366 / 0.524.  A K per query is
+// known on the device only: 262,144 rows of K from 1 to 64 0.870 / 0.519, from
+// 65 to 128 6.11 / 1.13, from {1, 8, 32, 128} 1.72 / 0.70; those past half the
+// buffer, which the setup lists apart, K = 200, 8.04 / 8.48.  (Given centres
+// are left alone: a service's mixed batch took 1.39 / 1.56.)
 bool choose_groups(const sphidx_lattice* lat, const sphidx_tables* tab, const QArgs& A, const Launch& ln) {
     if (ln.method != SPHIDX_METHOD_SPHERE || A.qx || A.Q < 16384u || A.stats || lat->ncells == 0) return false;
     if (A.mode != SPHIDX_MODE_RADIUS && (!A.stash || (!A.kk && A.k_u > 64u))) return false;

@@ -250,6 +250,10 @@ __host__ __device__ inline float knn_target(float k) {
     return a < b ? a : b;
 }
 
+// Pairs of the grouped count's hit buffer (eighths of sort_cap).
+constexpr uint32_t kHitEighths = 8;
+__host__ __device__ constexpr uint32_t group_hitcap(uint32_t cap) { return cap * kHitEighths / 8; }
+
 // Every query; with the tile kernel, the objects outside the region only (a
 // row that kernel does not keep is set up where it is walked, tile_query).
 // With `counters` (a launch of one block) the block first clears the counters
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
     }
     const uint32_t first = A.tiles ? L.cs[L.ncells] : 0u, stride = gridDim.x * blockDim.x;
     for (uint32_t i = first + blockIdx.x * blockDim.x + threadIdx.x; uni(i) < A.Q; i += stride) {
-    bool range_bad = false, fallback = false, to_list = false, longrow = false;
+    bool range_bad = false, fallback = false, to_list = false, longrow = false, large_k = false;
     if (i < A.Q) {
         uint32_t q[3], row, r, k;
         bool valid = true;
@@ -390,6 +394,12 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
             const float expect = 4.18879f * rc * rc * rc * ((float)L.n / (float)L.ncells);
             longrow = expect > 1.25f * (float)A.sort_cap;
         }
+        // a K-NN row of the sphere tables that the groups never take (K past
+        // half their buffer): straight onto the last list of a grouped count,
+        // in the queries' order (262,144 rows of K = 200 through both grouped
+        // rounds' lists took 9.18 ms, 0.78 of it to pass them on; one query per
+        // wavefront 8.04, this way 8.48)
+        large_k = METHOD != kPaper && A.group && valid && knn && sphere && k > group_hitcap(A.sort_cap) / 2u;
         uint32_t tb = 0, tend = 0, kb = 0, kend = 0;
         if (METHOD == kPaper && sphere && valid) {
             // the paper's tables (Section III.A): with d = r / e, the unshaved
@@ -471,6 +481,13 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
         if (lane_id() == 0) base = atomicAdd(A.lq_count, (uint32_t)__popcll(gm));
         base = uni(base);
         if (longrow) A.lq[base + lanes_below(gm)] = i;
+    }
+    const uint64_t km = __ballot(large_k);
+    if (km) {
+        uint32_t base = 0;
+        if (lane_id() == 0) base = atomicAdd(A.long_count, (uint32_t)__popcll(km));
+        base = uni(base);
+        if (large_k) A.longq[base + lanes_below(km)] = i;
     }
     if (__ballot(range_bad) && lane_id() == 0) atomicOr(L.status, SPHIDX_FLAG_RANGE);
     if (__ballot(fallback) && lane_id() == 0) atomicOr(L.status, SPHIDX_FLAG_FALLBACK);
@@ -1600,7 +1617,7 @@ __global__ __launch_bounds__(256) void count_kernel(LatArgs L, TabArgs T, QArgs 
 
 constexpr uint32_t kGroup = 8, kGroupBits = 3;
 // hit buffer keys and rows per group, in eighths of sort_cap
-constexpr uint32_t kHitEighths = 8, kRowEighths = 6;
+constexpr uint32_t kRowEighths = 6;
 constexpr uint32_t kMaxHitCap = 256 * kHitEighths / 8;
 // The group's hit buffer holds sort_cap keys, and a group ends before its
 // rows would exceed 3/4 of sort_cap.  When the hits overflow the buffer the
@@ -1640,7 +1657,6 @@ constexpr uint32_t kMaxHitCap = 256 * kHitEighths / 8;
 // per-slot counters, the 64-word owner map, then (stash) the hit keys in
 // arrival order, the same by bucket, and the bucket counts, or (no stash)
 // sort_cap 16-byte row records.
-__host__ __device__ constexpr uint32_t group_hitcap(uint32_t cap) { return cap * kHitEighths / 8; }
 __host__ __device__ constexpr uint32_t group_rows(uint32_t cap) { return cap * kRowEighths / 8; }
 // rows per chunk of the walk (at most 256): their 16-byte records
 // fill the bucket buffer and the bucket counts, both free until the sort
@@ -1722,6 +1738,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                     extra = true;
                 } else if (METHOD == kSphere && !sph) {
                     // counted by the fallback list's kernel
+                } else if (KNN && !FROM_LIST && (flags & F_KNN) && sph && d1.y > hitcap / 2u) {
+                    // listed by the setup for the one-query-per-wave kernel
                 } else if (KNN && (flags & F_KNN)) {
                     // K-NN (sphere tables, K up to half the buffer):
                     // a radius row at the first search radius d2.y, the
@@ -1730,7 +1748,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                     // object is farther)
                     const uint64_t b2 = (uint64_t)d2.y * d2.y;
                     const uint32_t b2bits = b2 ? 64u - (uint32_t)__builtin_clzll(b2) : 0u;
-                    if (!sph || (flags & F_LIST) || b2bits > d2bits || 2u * d1.y > hitcap) {
+                    if (!sph || (flags & F_LIST) || b2bits > d2bits) {
                         extra = true;
                     } else {
                         mine = true;
