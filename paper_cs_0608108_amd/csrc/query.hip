@@ -1194,8 +1194,7 @@ __device__ __forceinline__ uint32_t sort_bucket(uint64_t d2, float scale, uint32
 }
 
 __device__ void bucket_sort_store(const uint64_t* td, const uint32_t* ti, uint64_t* sd, uint32_t* si, uint32_t* hist,
-                                  uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2,
-                                  uint32_t limit = ~0u) {
+                                  uint32_t n, uint64_t r2, uint32_t* dst_ids, int64_t* dst_d2) {
     const uint32_t lane = lane_id();
     if (n == 0) return;
     const float scale = r2 > 0 ? (float)n / (float)r2 : 0.0f;
@@ -1240,7 +1239,6 @@ __device__ void bucket_sort_store(const uint64_t* td, const uint32_t* ti, uint64
         const uint32_t lo = hist[b], hi = b + 1 < n ? hist[b + 1] : n;
         uint32_t rank = lo;
         for (uint32_t j = lo; j < hi; ++j) rank += key_less(sd[j], si[j], d, id) ? 1u : 0u;
-        if (rank >= limit) continue;
         dst_ids[rank] = id;
         if (dst_d2) dst_d2[rank] = (int64_t)d;
     }
@@ -1424,16 +1422,15 @@ __device__ void sort_small_store(const uint64_t* td, const uint32_t* ti, uint64_
     wave_sync();
 }
 
-// Order the n <= cap pairs of one row by (dist^2, id) and store them (the first
-// `limit` of them, at least 64) at dst.
+// Order the n <= cap pairs of one row by (dist^2, id) and store them at dst.
 __device__ __forceinline__ void sort_row_store(const uint64_t* td, const uint32_t* ti, uint64_t* sd, uint32_t* si,
                                                uint32_t* hist, uint32_t n, uint64_t r2, uint32_t idbits,
-                                               uint32_t* dst_ids, int64_t* dst_d2, uint32_t limit = ~0u) {
+                                               uint32_t* dst_ids, int64_t* dst_d2) {
     const uint32_t r2bits = r2 ? 64u - (uint32_t)__builtin_clzll(r2) : 0u;
     if (n <= 64 && r2bits + idbits <= 64)
-        sort_small_store(td, ti, sd, n, idbits, dst_ids, dst_d2);  // (n <= 64: `limit` is more)
+        sort_small_store(td, ti, sd, n, idbits, dst_ids, dst_d2);
     else
-        bucket_sort_store(td, ti, sd, si, hist, n, r2, dst_ids, dst_d2, limit);
+        bucket_sort_store(td, ti, sd, si, hist, n, r2, dst_ids, dst_d2);
 }
 
 // FROM_LIST: a query list (the sphere method's fallback queries, scanned with
@@ -2958,12 +2955,11 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
     char* wb = smem + table_lds_bytes<TLDS>(T) + (size_t)wave * ((size_t)cap * 24 + 64 * 12 + 256);
     uint64_t* tdA = (uint64_t*)wb;
     uint64_t* tdB = tdA + cap;
-    uint32_t* tiA = (uint32_t*)(tdB + cap);
+    uint64_t* bd = tdB + cap;
+    uint32_t* tiA = (uint32_t*)(bd + 64);
     uint32_t* tiB = tiA + cap;
-    uint64_t* bd = (uint64_t*)(tiB + cap);
-    uint32_t* bi = (uint32_t*)(bd + 64);
+    uint32_t* bi = tiB + cap;
     uint32_t* own = bi + 64;
-    uint32_t* hist = (uint32_t*)bd;  // cap <= 256 words over bd, bi and own, between walks
     if (A.row_ptr[A.Q] > A.capacity) {
         if (threadIdx.x == 0) atomicOr(L.status, SPHIDX_FLAG_CAPACITY);
         return;
@@ -2979,7 +2975,6 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
     const uint32_t nbig = FROM_LIST || from_walk ? uni(*A.big_count) : 0u;
     const uint32_t* rest = FROM_LIST ? A.list : A.walkq;
     const uint32_t nq = FROM_LIST ? nbig + uni(*A.list_count) : from_walk ? nbig + uni(*A.walk_count) : A.Q;
-    const uint32_t idbits = L.n > 1 ? 32u - (uint32_t)__builtin_clz(L.n - 1u) : 0u;  // ids are below n
     for_each_query(nq, A, queue_set(A, kQTopm), [&](uint32_t ti_) {
         const uint32_t qi =
             ti_ < nbig ? uni(A.bigq[ti_]) : FROM_LIST || from_walk ? uni(rest[ti_ - nbig]) : ti_;
@@ -2998,36 +2993,6 @@ __global__ __launch_bounds__(256) void topm_kernel(LatArgs L, TabArgs T, QArgs A
         uint64_t ld = 0;
         uint32_t li = 0;
         uint32_t written = 0;
-        if ((s.flags & F_KBOUND) && rowlen > 64u && rowlen <= cap) {
-            // the count pass left a radius that holds K objects, few more of
-            // them: collected whole and sorted once, the first K stored (in
-            // windows when the buffer does not hold them)
-            const uint64_t kb2 = min(s.r2, sq(s.kbr));
-            uint32_t n = 0, cand = 0, walked = 0;
-            walk<METHOD, TLDS, true>(L, T, tab_lds, s, false, walked, [&]() { return kb2; },
-                                     [&](const RowRef& r) -> bool {
-                return for_candidates(L, r.st0, r.cnt0, r.st1, r.cnt1, own, cand,
-                                      [&](bool act, uint32_t p, const uint4& P) -> bool {
-                    const uint64_t d2 = obj_dist2(aw, s, P);
-                    const bool hit = act && d2 <= kb2 && p != s.self;
-                    const uint64_t hm = __ballot(hit);
-                    const uint32_t at = lanes_below(hm, n);
-                    if (hit && at < cap) {
-                        tdA[at] = d2;
-                        tiA[at] = P.w;
-                    }
-                    n += (uint32_t)__popcll(hm);
-                    return n > cap;
-                });
-            });
-            wave_sync();
-            if (n >= rowlen && n <= cap) {
-                sort_row_store(tdA, tiA, tdB, tiB, hist, n, kb2, idbits, A.out_ids + rb,
-                               A.out_d2 ? A.out_d2 + rb : nullptr, rowlen);
-                wave_sync();
-                return;
-            }
-        }
         while (written < rowlen) {
             const uint32_t M = min(cap, rowlen - written);
             const uint32_t target = written + M;
