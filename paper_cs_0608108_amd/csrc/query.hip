@@ -2211,6 +2211,7 @@ struct TileArgs {
     uint32_t cl, wy, wz;    // log2 of a chunk's columns and of a strip's rows in y and z
     uint32_t nchunks;
     uint32_t part;          // queries per work item (a multiple of kTileQ)
+    uint32_t mean;          // queries per chunk
     uint32_t d2bits;        // bits of dist^2 in a key: those of the largest r^2
 };
 
@@ -2225,11 +2226,15 @@ __device__ __forceinline__ uint32_t tile_cell(const LatArgs& L, const TileArgs& 
     return pack_cell(L, (cx << TA.cl) + col, y, z);
 }
 
-// Queries per work item of a chunk of T queries: a multiple of kTileQ, at
+// Queries per work item of a chunk of T queries: a multiple of kTileQ, fewer in
+// chunks of half as many again as the mean (their rows are as much longer, and
+// one wavefront would be left with an item for long after the others: 1,048,576
+// agents in 1,024 clusters, r = 3 cells, count pass 4.5 ms, this way 2.8), at
 // most 1,024 items per chunk.
 __device__ __forceinline__ uint32_t tile_part(const TileArgs& TA, uint32_t T) {
-    const uint32_t per = (T + 1023u) >> 10;
-    return max(TA.part, (per + kTileQ - 1u) & ~(kTileQ - 1u));
+    const uint32_t least = (T + 1023u) >> 10;
+    const uint32_t part = T > TA.mean + TA.mean / 2u ? (uint32_t)((uint64_t)TA.part * TA.mean / T) : TA.part;
+    return (max(max(part, least), 1u) + kTileQ - 1u) & ~(kTileQ - 1u);
 }
 
 // One thread per chunk: its work items, chunk | part << 22.  The objects left out
@@ -3670,6 +3675,7 @@ bool tile_plan(const LatArgs& L, const TabArgs& T, const QArgs& q, TileArgs& TA)
     }
     TA.nchunks = L.ncells >> (TA.cl + TA.wy + TA.wz);
     TA.part = std::min(256u, std::max(kTileQ, q.Q / (tile_blocks() * 4u) / kTileQ * kTileQ));
+    TA.mean = q.Q / TA.nchunks;
     return TA.nchunks <= (1u << 22);
 }
 
