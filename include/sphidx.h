@@ -334,7 +334,8 @@ typedef struct {
                             the buffer (K-NN: rows kept, and one K of at most 64 or a K per
                             query, of which those past sort_cap / 2 are searched one per
                             wavefront), else one query per wavefront (always with
-                            per-query statistics) */
+                            per-query statistics);
+                            2: one query per wavefront */
     /* METHOD_AUTO (Appendix: weighting factor and reversal distances).  A radius query takes
      * the sphere when select_weight/256 * (sphere cells) <= (cube cells), else the cube; then
      * the non-empty list instead if it holds fewer cells than the one chosen (plain counts).

@@ -125,7 +125,7 @@ sphidx_status resolve_launch(const sphidx_launch* in, const sphidx_tables* tab, 
     o.no_stash = in ? in->no_stash : 0u;
     if (o.no_stash > 1) return SPHIDX_ERR_INVALID_ARG;
     o.grouped = in ? in->grouped : 0u;
-    if (o.grouped > 1) return SPHIDX_ERR_INVALID_ARG;
+    if (o.grouped > 2) return SPHIDX_ERR_INVALID_ARG;
     o.long_waves = (in && in->long_row_waves) ? in->long_row_waves : 4u;
     if (!(o.long_waves == 1 || o.long_waves == 2 || o.long_waves == 4 || o.long_waves == 8))
         return SPHIDX_ERR_INVALID_ARG;
@@ -404,7 +404,7 @@ sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables*
     // shortcut, which the grouped kernel does not implement)
     // (the paper's cell tables are walked one query per wavefront)
     A.group = pass == 0 && ln.persistent && !A.interior && !T.paper &&
-              (ln.grouped || choose_groups(lat, tab, A, ln));
+              (ln.grouped == 1 || (ln.grouped == 0 && choose_groups(lat, tab, A, ln)));
     if (pass == 0) {
         s = dev_err(launch_query_pass(0, L, T, A, ln.waves, ln.bpc, st, ln.ev_begin, ln.ev_end));
         if (s != SPHIDX_OK) return s;

@@ -356,7 +356,7 @@ class LaunchConfig:
     stats: torch.Tensor | None = None
     events: tuple | None = None  # (begin, end) torch.cuda.Event around the pass's main kernel
     no_stash: int = 0
-    grouped: int = 0
+    grouped: int = 0  # 0: the library's choice, 1: groups, 2: one query per wavefront
     select_weight: int = 0  # METHOD_AUTO: Q8 weight of the sphere's cell count (0 = 256)
     reversal_fx: int = 0
     knn_reversal_fx: int = 0
