@@ -331,9 +331,10 @@ typedef struct {
                             wavefront; the stash needs K pairs per such row);
                             0: the library's choice: groups for all-agents batches of the
                             sphere method from 16,384 queries on whose expected rows fit
-                            the buffer (K-NN: rows kept, and one K of at most 64 or a K per
-                            query, of which those past sort_cap / 2 are searched one per
-                            wavefront), else one query per wavefront (always with
+                            the buffer (K-NN: rows kept, from 65,536 queries on unless
+                            K = 1, one K of at most 64 or a K per query, of which those
+                            past sort_cap / 2 are searched one per wavefront, and objects
+                            dense enough), else one query per wavefront (always with
                             per-query statistics);
                             2: one query per wavefront */
     /* METHOD_AUTO (Appendix: weighting factor and reversal distances).  A radius query takes

@@ -296,12 +296,32 @@ void plan_stash(QArgs& A, const sphidx_csr* csr, const Launch& ln, bool interior
     A.stash_chunk = stash_chunk(A.stash_region, (uint64_t)device_cu_count() * ln.bpc * ln.waves, ln.cap);
 }
 
+// Objects per cell from which K-NN rows are faster in groups than one per
+// wavefront: below, too many rows fall short of K inside their first radius and
+// go from round to round, and past K / 130 a row has too many cells.  Count +
+// write of uniform clouds, groups over one per wavefront: 128^3, 0.125 objects
+// per cell, K = 4 0.96, 10 0.75, 16 0.92, 24 1.05, 64 1.14, 0.25 per cell 0.82,
+// 0.67, 0.76, 0.86, 1.00; 256^3, 0.125 per cell 0.96, 0.83, 1.02, 1.27, 1.36,
+// 0.25 per cell K = 16 0.82, 32 1.04, 64 1.15, 0.376 per cell K = 40 0.92, 64
+// 1.05, 0.5 per cell K = 64 0.91; 105,000 points, 0.05 per cell, 1.06 to 1.38.
+double knn_group_density(const QArgs& A) {
+    if (A.kk) return 0.3;
+    return A.k_u <= 1u ? 0.0 : A.k_u <= 16u ? 0.2 : std::max(0.3, A.k_u / 130.0);
+}
+
 // Whether the count pass takes a batch in groups when the launch leaves it to
 // the library (grouped = 0): all-agents batches, whose neighbouring queries
 // share rows and candidates, of 16,384 queries and more (below, one launch
 // more costs what the groups save), with rows that fit the hit buffer; K-NN
-// only when its rows are kept, as a row short of K is searched again.  Count +
-// write in ms, one query per wavefront against groups (or tiles), cyclic and
+// only when its rows are kept, as a row short of K is searched again, for K > 1
+// from 65,536 queries on, as that is a chain of three kernels (uniform clouds,
+// K = 4, 16, 64: 17,000 points at 0.52 per cell 1.17, 1.32, 1.41 of the time of
+// one query per wavefront, 45,000 at 0.17 1.15, 1.31, 1.37, 98,765 at 0.38 0.94,
+// 0.84, 0.97; K = 1 0.22 to 0.78 from 17,000 points on), and where objects are
+// dense enough: by the mean density or, where that says no, by a sample on the
+// device, as a cloud's objects often fill few of the cells (210,000 points in
+// 64 clusters, 0.1 per cell: K = 2 to 64 0.55 to 0.78).  Count + write in ms,
+// one query per wavefront against groups (or tiles), cyclic and
 // clipped lattices: r = 2.5 cells at 0.5 objects per cell, 16 K queries 0.100 /
 // 0.082; r = 3, 131 K 0.230 / 0.166; r = 4 (135 pairs) 0.342 / 0.331, 227 pairs
 // 1.87 / 1.97; uneven radii to 4 cells, 1 M 1.22 / 0.79; K = 10, 99 K 0.321 /
@@ -309,15 +329,22 @@ void plan_stash(QArgs& A, const sphidx_csr* csr, const Launch& ln, bool interior
 // the stash r = 3 0.309 / 0.261 but K = 10 0.366 / 0.524.  A K per query is
 // known on the device only: 262,144 rows of K from 1 to 64 0.870 / 0.519, from
 // 65 to 128 6.11 / 1.13, from {1, 8, 32, 128} 1.72 / 0.70; those past half the
-// buffer, which the setup lists apart, K = 200, 8.04 / 8.48.  (Given centres
+// buffer, which the setup lists apart, K = 200, 8.04 / 8.11.  (Given centres
 // are left alone: a service's mixed batch took 1.39 / 1.56.)
-bool choose_groups(const sphidx_lattice* lat, const sphidx_tables* tab, const QArgs& A, const Launch& ln) {
-    if (ln.method != SPHIDX_METHOD_SPHERE || A.qx || A.Q < 16384u || A.stats || lat->ncells == 0) return false;
-    if (A.mode != SPHIDX_MODE_RADIUS && (!A.stash || (!A.kk && A.k_u > 64u))) return false;
-    if (A.mode == SPHIDX_MODE_KNN) return true;
-    const double r = (double)(A.rad ? tab->rmax_fx : A.rad_u) / (double)(1u << lat->desc.frac_bits);
-    const double hits = 4.18879 * r * r * r * (double)lat->n / (double)lat->ncells;
-    return hits <= (A.rad ? 0.75 : 0.625) * A.sort_cap;
+uint32_t choose_groups(const sphidx_lattice* lat, const sphidx_tables* tab, const QArgs& A, const Launch& ln) {
+    if (ln.method != SPHIDX_METHOD_SPHERE || A.qx || A.Q < 16384u || A.stats || lat->ncells == 0) return kGroupNone;
+    const double load = (double)lat->n / (double)lat->ncells;
+    uint32_t how = kGroupAll;
+    if (A.mode != SPHIDX_MODE_RADIUS) {
+        if (!A.stash || (!A.kk && A.k_u > 64u)) return kGroupNone;
+        if ((A.kk || A.k_u > 1u) && A.Q < 65536u) return kGroupNone;
+        if (load < knn_group_density(A)) how = kGroupSampled;
+    }
+    if (A.mode != SPHIDX_MODE_KNN) {
+        const double r = (double)(A.rad ? tab->rmax_fx : A.rad_u) / (double)(1u << lat->desc.frac_bits);
+        if (4.18879 * r * r * r * load > (A.rad ? 0.75 : 0.625) * A.sort_cap) return kGroupNone;
+    }
+    return how;
 }
 
 void* scan_tmp_of(sphidx_csr* csr, uint32_t Q) { return (char*)csr->workspace_dev + query_layout(Q).scan; }
@@ -403,8 +430,10 @@ sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables*
     // persistent schedule; not with per-query statistics or the interior
     // shortcut, which the grouped kernel does not implement)
     // (the paper's cell tables are walked one query per wavefront)
-    A.group = pass == 0 && ln.persistent && !A.interior && !T.paper &&
-              (ln.grouped == 1 || (ln.grouped == 0 && choose_groups(lat, tab, A, ln)));
+    A.group = kGroupNone;
+    if (pass == 0 && ln.persistent && !A.interior && !T.paper)
+        A.group = ln.grouped == 1 ? kGroupAll : ln.grouped == 0 ? choose_groups(lat, tab, A, ln) : kGroupNone;
+    A.group_dense = (float)knn_group_density(A);
     if (pass == 0) {
         s = dev_err(launch_query_pass(0, L, T, A, ln.waves, ln.bpc, st, ln.ev_begin, ln.ev_end));
         if (s != SPHIDX_OK) return s;

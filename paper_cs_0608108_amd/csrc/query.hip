@@ -182,10 +182,11 @@ __device__ __forceinline__ uint64_t sq(uint32_t g) { return (uint64_t)g * (uint6
 // walks only, which leave that word unused).  F_LONG: a radius row expected
 // to be longer than a wavefront's buffer, counted and kept one block per row.
 // F_WINDOW: a radius row that the block kernel of the write pass left to the
-// windowed top-M kernel.
+// windowed top-M kernel.  F_ALONE: a K-NN row of a grouped count that the setup
+// listed for the one-query-per-wave kernel.
 enum : uint32_t {
     F_VALID = 1u, F_KNN = 2u, F_SPHERE = 4u, F_OUTSIDE = 8u, F_LIST = 16u, F_KBOUND = 32u, F_LONG = 64u,
-    F_WINDOW = 128u
+    F_WINDOW = 128u, F_ALONE = 256u
 };
 
 struct Query {
@@ -213,7 +214,7 @@ __device__ __forceinline__ uint32_t pack_cell(const LatArgs& L, uint32_t x, uint
 }
 
 // Zero counter words [begin, end), by one block; the count pass also writes the
-// stash header (hdr != NULL: five words), inside the cleared range, after every
+// stash header (hdr != NULL: six words), inside the cleared range, after every
 // clear.  Counters sit SPHIDX_QSTRIDE words apart and only those words are
 // read: the others are left as they are.
 __device__ void clear_counters(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv, uint32_t tiles) {
@@ -226,12 +227,37 @@ __device__ void clear_counters(uint32_t* c, uint32_t begin, uint32_t end, uint32
         hdr[kHdrHasD2] = hv.z;
         hdr[kHdrD2Off] = hv.w;
         hdr[kHdrTiles] = tiles;
+        hdr[kHdrSparse] = 0u;
     }
 }
 
+// `dense` > 0: whether half of 1,024 objects, of every part of the lattice, have
+// fewer than `dense` other objects per cell in the 33 cells along x around their
+// own (kGroupSampled; the header's sparse word).
 __global__ void clear_counters_kernel(uint32_t* c, uint32_t begin, uint32_t end, uint32_t* hdr, uint4 hv,
-                                      uint32_t tiles) {
+                                      uint32_t tiles, LatArgs L, float dense) {
+    __shared__ uint32_t votes;
+    if (threadIdx.x == 0) votes = 0u;
     clear_counters(c, begin, end, hdr, hv, tiles);
+    if (!(dense > 0.0f)) return;
+    __syncthreads();
+    const uint32_t in = L.cs[L.ncells], per = 1024u / blockDim.x;  // objects of the region
+    for (uint32_t j = 0; j < per && in > 0u; ++j) {
+        const uint4 P = L.pts[(uint32_t)(((uint64_t)(threadIdx.x * per + j) * in) >> 10)];
+        const uint32_t cx = P.x >> L.F, nx = 1u << L.lg[0];
+        const uint32_t below = min(cx, 16u), above = min(nx - 1u - cx, 16u);
+        const uint32_t home = pack_cell(L, cx, P.y >> L.F, P.z >> L.F);
+        const uint32_t others = L.cs[home + above + 1u] - L.cs[home - below] - 1u;
+        if ((float)others < dense * (float)(below + above + 1u)) atomicAdd(&votes, 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && votes > 512u) hdr[kHdrSparse] = 1u;
+}
+
+// Whether the sample left a batch that could go in groups to one query per
+// wavefront.
+__device__ __forceinline__ bool left_sparse(const QArgs& A) {
+    return A.group == kGroupSampled && uni(A.stash_hdr[kHdrSparse]) != 0u;
 }
 
 // One thread per query: centre, radius, K, method and walk extent.
@@ -267,7 +293,7 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
     }
     const uint32_t first = A.tiles ? L.cs[L.ncells] : 0u, stride = gridDim.x * blockDim.x;
     for (uint32_t i = first + blockIdx.x * blockDim.x + threadIdx.x; uni(i) < A.Q; i += stride) {
-    bool range_bad = false, fallback = false, to_list = false, longrow = false, large_k = false;
+    bool range_bad = false, fallback = false, to_list = false, longrow = false, alone = false;
     if (i < A.Q) {
         uint32_t q[3], row, r, k;
         bool valid = true;
@@ -399,7 +425,8 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
         // in the queries' order (262,144 rows of K = 200 through both grouped
         // rounds' lists took 9.18 ms, 0.78 of it to pass them on; one query per
         // wavefront 8.04, this way 8.48)
-        large_k = METHOD != kPaper && A.group && valid && knn && sphere && k > group_hitcap(A.sort_cap) / 2u;
+        alone = METHOD != kPaper && A.group && valid && knn && sphere && k > group_hitcap(A.sort_cap) / 2u &&
+                !left_sparse(A);
         uint32_t tb = 0, tend = 0, kb = 0, kend = 0;
         if (METHOD == kPaper && sphere && valid) {
             // the paper's tables (Section III.A): with d = r / e, the unshaved
@@ -457,7 +484,8 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
             A.method_out[row] = !valid ? 0xFFFFFFFFu
                                        : sphere ? SPHIDX_METHOD_SPHERE : list ? SPHIDX_METHOD_LIST : SPHIDX_METHOD_CUBE;
         const uint32_t flags = (valid ? F_VALID : 0u) | (knn ? F_KNN : 0u) | (sphere ? F_SPHERE : 0u) |
-                               (outside ? F_OUTSIDE : 0u) | (list ? F_LIST : 0u) | (longrow ? F_LONG : 0u);
+                               (outside ? F_OUTSIDE : 0u) | (list ? F_LIST : 0u) | (longrow ? F_LONG : 0u) |
+                               (alone ? F_ALONE : 0u);
         uint4* d = A.desc + 4 * (size_t)i;
         d[0] = make_uint4(q[0], q[1], q[2], row);
         d[1] = make_uint4(r, k, flags, tb);
@@ -482,12 +510,12 @@ __global__ __launch_bounds__(1024) void setup_kernel(LatArgs L, TabArgs T, QArgs
         base = uni(base);
         if (longrow) A.lq[base + lanes_below(gm)] = i;
     }
-    const uint64_t km = __ballot(large_k);
+    const uint64_t km = __ballot(alone);
     if (km) {
         uint32_t base = 0;
         if (lane_id() == 0) base = atomicAdd(A.long_count, (uint32_t)__popcll(km));
         base = uni(base);
-        if (large_k) A.longq[base + lanes_below(km)] = i;
+        if (alone) A.longq[base + lanes_below(km)] = i;
     }
     if (__ballot(range_bad) && lane_id() == 0) atomicOr(L.status, SPHIDX_FLAG_RANGE);
     if (__ballot(fallback) && lane_id() == 0) atomicOr(L.status, SPHIDX_FLAG_FALLBACK);
@@ -1442,6 +1470,7 @@ __device__ __forceinline__ void sort_row_store(const uint64_t* td, const uint32_
 template <int METHOD, bool TLDS, bool FROM_LIST, bool STASH, bool KSTASH>
 __global__ __launch_bounds__(256) void count_kernel(LatArgs L, TabArgs T, QArgs A) {
     extern __shared__ __align__(16) char smem[];
+    if (KSTASH && !FROM_LIST && A.group == kGroupSampled && !left_sparse(A)) return;  // taken in groups
     const uint32_t* tab_lds = stage_table<TLDS>(T, smem);
     const uint32_t wave = threadIdx.x >> 6;
     const uint32_t cap = A.sort_cap;
@@ -1680,6 +1709,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                                                                                                  TabArgs T,
                                                                                                  QArgs A) {
     extern __shared__ __align__(16) char smem[];
+    if (KNN && !FROM_LIST && left_sparse(A)) return;
     const uint32_t* tab_lds = stage_table<TLDS>(T, smem);
     const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
     const uint32_t hitcap = group_hitcap(A.sort_cap), grows = group_rows(A.sort_cap);  // hitcap <= kMaxHitCap
@@ -1735,7 +1765,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
                     extra = true;
                 } else if (METHOD == kSphere && !sph) {
                     // counted by the fallback list's kernel
-                } else if (KNN && !FROM_LIST && (flags & F_KNN) && sph && d1.y > hitcap / 2u) {
+                } else if (KNN && !FROM_LIST && (flags & F_ALONE)) {
                     // listed by the setup for the one-query-per-wave kernel
                 } else if (KNN && (flags & F_KNN)) {
                     // K-NN (sphere tables, K up to half the buffer):
@@ -3838,7 +3868,9 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
         const uint4 hv = make_uint4(q.stash, q.stash ? q.stash_region * SPHIDX_NREGION : 0u, q.stash_d2 ? 1u : 0u,
                                     q.stash_d2 ? (uint32_t)(((char*)q.stash_d2 - q.stash_base) / 256) : 0u);
         const bool setup = q.Q > 0 && !(q.tiles && L.cyc == 7u), one = setup && q.Q <= kSmallSetup;
-        if (!one) clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, 0u, SPHIDX_COUNTER_WORDS, q.stash_hdr, hv, q.tiles);
+        if (!one)
+            clear_counters_kernel<<<1, 256, 0, st>>>(q.queues, 0u, SPHIDX_COUNTER_WORDS, q.stash_hdr, hv, q.tiles, L,
+                                                     q.group == kGroupSampled ? q.group_dense : 0.0f);
         if (setup) {
             const uint32_t threads = one ? std::max(256u, (q.Q + 63u) & ~63u) : 256u;
             const uint32_t blocks = one ? 1u : q.tiles ? std::min((q.Q + 255u) / 256u, 512u) : (q.Q + 255u) / 256u;
@@ -3894,6 +3926,10 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
                                   : (either ? SPHIDX_PICK(group_count_kernel, variant, kEither, , false, false, false)
                                             : SPHIDX_PICK(group_count_kernel, variant, kSphere, , false, false, false)),
                                q.Q, q, w, b, gl, st, L, T);
+            // (one of the two finds nothing to do)
+            if (e == hipSuccess && q.group == kGroupSampled)
+                e = launch_ptr(SPHIDX_PICKS(count_kernel, variant, kSphere, , false, true, true), q.Q, q, w, b,
+                               query_lds_bytes(lp, q.sort_cap, w, tb), st, L, T);
             if (e == hipSuccess) e = mark(ev_end);
             if (e != hipSuccess) return e;
             if (long_rows_possible() && (e = launch_long(true, long_list())) != hipSuccess) return e;

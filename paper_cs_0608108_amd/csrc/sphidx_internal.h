@@ -160,7 +160,8 @@ struct QArgs {
     uint32_t tile;
     uint32_t sort_cap;
     uint32_t interior;  // count pass: count wholly-inside cells without reading them
-    uint32_t group;     // count pass: radius queries in groups per wavefront
+    uint32_t group;     // count pass: queries in groups per wavefront (kGroupNone, kGroupAll, kGroupSampled)
+    float group_dense;  // kGroupSampled: objects per cell from which the groups take the batch
     uint32_t select;    // setup: 0 = the kernel's method, 1 = choose by volume, 2 = cell list
     uint32_t weight;    // volume choice: sphere cells x weight / 256 against cube cells
     uint32_t rev;       // volume choice: radius queries below this skip the sphere
@@ -174,7 +175,11 @@ struct QArgs {
 
 // Stash header words (in the counter block): written by the count pass,
 // read by the write pass, which therefore needs no host-side state.
-enum : uint32_t { kHdrMode = 0, kHdrElems = 1, kHdrHasD2 = 2, kHdrD2Off = 3, kHdrTiles = 4 };
+enum : uint32_t { kHdrMode = 0, kHdrElems = 1, kHdrHasD2 = 2, kHdrD2Off = 3, kHdrTiles = 4, kHdrSparse = 5 };
+
+// QArgs::group: one query per wavefront, groups, or groups unless a sample of
+// the lattice finds it sparse (decided on the device, kHdrSparse).
+enum : uint32_t { kGroupNone = 0, kGroupAll = 1, kGroupSampled = 2 };
 
 #define SPHIDX_NXCD 8           // XCDs of the MI355X: blocks are dispatched to them in turn
 #define SPHIDX_NQUEUE 64        // work queues per set, 8 per XCD: queue q is served by the blocks of XCD q mod 8

@@ -66,7 +66,7 @@ def test_large_k_rows_pass_no_grouped_round(sx, mask):
     kd = sx.to_dev_u32(k)
     q = sx.make_queries(n, None, 6 << F, kd, sx.MODE_KNN)
     buf = sx.QueryBuffers(n, 0, want_dist2=False, stash_pairs=int(k.sum()))
-    sx.count(lat, tab, q, buf, sx.LaunchConfig())
+    sx.count(lat, tab, q, buf, sx.LaunchConfig(grouped=1))
     left = lists(buf)
     assert left["extra"] == 0 and left["long"] == n, left
     del kd

@@ -23,11 +23,11 @@ def sx():
 def test_one_query_per_wavefront_on_request(sx, orc, mask):
     import torch
     rng = np.random.default_rng(1500 + mask)
-    log2, F, n = (5, 5, 5), 12, 17000
+    log2, F, n = (5, 5, 5), 12, 66000
     pts = tuple(rng.integers(0, 32 << F, n).astype(np.uint32) for _ in range(3))
     lat = lattice(sx, log2, F, mask, pts, cell_list=False)
     tab = sx.Tables(lat, 2, 4 << F)
-    r = 5 << (F - 1)
+    r = 3 << (F - 1)
     g = orc.Grid(orc.Lattice(log2, F, mask), pts)
     ref = g.radius(r)
     refk = g.knn(np.full(n, 20, np.uint32), np.full(n, 4 << F, np.uint32))
