@@ -382,6 +382,14 @@ size_t sphidx_query_workspace_bytes(uint32_t Q);
 sphidx_status sphidx_count(const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
                            sphidx_csr* csr, const sphidx_launch* launch, void* stream);
 
+/* The name of the kernel that sphidx_count takes for the rows of this call
+ * ("tile_count_kernel", "group_count_kernel", "count_kernel", or, where a
+ * sample of the lattice decides on the device, both of the last two), as the
+ * launch leaves the choice to the library; NULL for a call that it refuses.
+ * Host only: nothing is enqueued. */
+const char* sphidx_count_kernel(const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
+                                sphidx_csr* csr, const sphidx_launch* launch);
+
 /* Pass 2: fill ids (and dist2) of every row using row_ptr and the query
  * descriptors and lists that sphidx_count left in the workspace: same
  * inputs, same launch method, same workspace, unchanged in between.  If

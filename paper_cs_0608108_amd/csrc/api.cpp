@@ -397,11 +397,21 @@ sphidx_status attach_device(sphidx_tables* t) {
     return tables_upload(t);
 }
 
-sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
-                       sphidx_csr* csr, const sphidx_launch* launch, hipStream_t st) {
+struct Pass {
+    Launch ln;
+    LatArgs L;
+    TabArgs T;
+    QArgs A;
+};
+
+// The checks and kernel arguments of one pass.  Tables not yet on the device
+// are uploaded with `upload` (the arguments of a pass that is only planned
+// point nowhere).
+sphidx_status plan_pass(int pass, const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
+                        sphidx_csr* csr, const sphidx_launch* launch, bool upload, Pass& p) {
     sphidx_status s = check_queries(lat, q, csr);
     if (s != SPHIDX_OK) return s;
-    Launch ln;
+    Launch& ln = p.ln;
     s = resolve_launch(launch, tab, ln);
     if (s != SPHIDX_OK) return s;
     if (pass == 1 && csr->capacity > 0 && !csr->ids_dev) return SPHIDX_ERR_INVALID_ARG;
@@ -409,17 +419,16 @@ sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables*
     const bool tables = ln.method == SPHIDX_METHOD_SPHERE || ln.method == SPHIDX_METHOD_AUTO ||
                         ln.method == SPHIDX_METHOD_PAPER64;
     if (ln.method == SPHIDX_METHOD_LIST && !lat->cell_list) return SPHIDX_ERR_INVALID_ARG;
-    if (tab && tables && !tab->d_rows) {
+    if (upload && tab && tables && !tab->d_rows) {
         s = tables_upload(const_cast<sphidx_tables*>(tab));
         if (s != SPHIDX_OK) return s;
     }
-    note_stream(lat, (void*)st);
-    LatArgs L = lat_args(lat);
-    TabArgs T = tab_args(tables ? tab : nullptr);
+    p.L = lat_args(lat);
+    TabArgs& T = p.T = tab_args(tables ? tab : nullptr);
     T.lds = ln.tab_lds ? 1u : 0u;
     T.lds_chunk = ln.lds_chunk;
     T.paper = ln.method == SPHIDX_METHOD_PAPER64 ? 1u : 0u;
-    QArgs A = q_args(q, csr, ln);
+    QArgs& A = p.A = q_args(q, csr, ln);
     if (pass == 0) plan_stash(A, csr, ln, ln.interior == 2);
     // counting wholly-inside cells whole saves object reads but costs a
     // second extent per row: worth it once cells hold an object or more
@@ -434,12 +443,18 @@ sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables*
     if (pass == 0 && ln.persistent && !A.interior && !T.paper)
         A.group = ln.grouped == 1 ? kGroupAll : ln.grouped == 0 ? choose_groups(lat, tab, A, ln) : kGroupNone;
     A.group_dense = (float)knn_group_density(A);
-    if (pass == 0) {
-        s = dev_err(launch_query_pass(0, L, T, A, ln.waves, ln.bpc, st, ln.ev_begin, ln.ev_end));
-        if (s != SPHIDX_OK) return s;
-        return dev_err(launch_scan_i64(csr->row_ptr_dev, q->count, scan_tmp_of(csr, q->count), st));
-    }
-    return dev_err(launch_query_pass(1, L, T, A, ln.waves, ln.bpc, st, ln.ev_begin, ln.ev_end));
+    return SPHIDX_OK;
+}
+
+sphidx_status run_pass(int pass, const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
+                       sphidx_csr* csr, const sphidx_launch* launch, hipStream_t st) {
+    Pass p;
+    sphidx_status s = plan_pass(pass, lat, tab, q, csr, launch, true, p);
+    if (s != SPHIDX_OK) return s;
+    note_stream(lat, (void*)st);
+    s = dev_err(launch_query_pass(pass, p.L, p.T, p.A, p.ln.waves, p.ln.bpc, st, p.ln.ev_begin, p.ln.ev_end));
+    if (s != SPHIDX_OK || pass != 0) return s;
+    return dev_err(launch_scan_i64(csr->row_ptr_dev, q->count, scan_tmp_of(csr, q->count), st));
 }
 
 }  // namespace
@@ -689,6 +704,13 @@ size_t sphidx_query_stash_bytes(uint64_t pairs, int want_dist2) {
 sphidx_status sphidx_count(const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
                            sphidx_csr* csr, const sphidx_launch* launch, void* stream) {
     return run_pass(0, lat, tab, q, csr, launch, (hipStream_t)stream);
+}
+
+const char* sphidx_count_kernel(const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,
+                                sphidx_csr* csr, const sphidx_launch* launch) {
+    Pass p;
+    if (plan_pass(0, lat, tab, q, csr, launch, false, p) != SPHIDX_OK) return nullptr;
+    return count_kernel_name(p.L, p.T, p.A);
 }
 
 sphidx_status sphidx_write(const sphidx_lattice* lat, const sphidx_tables* tab, const sphidx_queries* q,

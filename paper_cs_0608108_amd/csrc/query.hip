@@ -3815,6 +3815,14 @@ size_t query_lds_bytes(int pass, uint32_t cap, uint32_t waves, size_t table_byte
     return table_bytes + per * waves;
 }
 
+const char* count_kernel_name(const LatArgs& L, const TabArgs& T, const QArgs& q) {
+    TileArgs TA;
+    if (tile_plan(L, T, q, TA)) return "tile_count_kernel";
+    return q.group == kGroupAll       ? "group_count_kernel"
+           : q.group == kGroupSampled ? "group_count_kernel or count_kernel"
+                                      : "count_kernel";
+}
+
 hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const QArgs& q_in,
                              uint32_t waves_per_block, uint32_t blocks_per_cu, hipStream_t st,
                              hipEvent_t ev_begin, hipEvent_t ev_end) {

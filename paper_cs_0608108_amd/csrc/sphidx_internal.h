@@ -225,6 +225,8 @@ size_t scan_i64_tmp_bytes(uint32_t n);
 hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const QArgs& q,
                              uint32_t waves_per_block, uint32_t blocks_per_cu, hipStream_t st,
                              hipEvent_t ev_begin, hipEvent_t ev_end);
+// Which kernel launch_query_pass(0, ...) counts the rows with.
+const char* count_kernel_name(const LatArgs& L, const TabArgs& T, const QArgs& q);
 hipError_t launch_build_records(const sphidx_lattice* lat, const uint4* recs, uint32_t n, hipStream_t st);
 hipError_t launch_move_records(const sphidx_lattice_desc& d, uint64_t seed, uint32_t* step_dev, const uint4* src,
                                uint4* dst, uint32_t n, hipStream_t st);

@@ -95,6 +95,8 @@ SIGNATURES = {
     "sphidx_query_stash_bytes": (SZ, [ctypes.c_uint64, ctypes.c_int]),
     "sphidx_count": (ctypes.c_int, [P, P, ctypes.POINTER(Queries), ctypes.POINTER(CSRDesc),
                                     ctypes.POINTER(LaunchDesc), P]),
+    "sphidx_count_kernel": (ctypes.c_char_p, [P, P, ctypes.POINTER(Queries), ctypes.POINTER(CSRDesc),
+                                              ctypes.POINTER(LaunchDesc)]),
     "sphidx_write": (ctypes.c_int, [P, P, ctypes.POINTER(Queries), ctypes.POINTER(CSRDesc),
                                     ctypes.POINTER(LaunchDesc), P]),
     "sphidx_query": (ctypes.c_int, [P, P, ctypes.POINTER(Queries), ctypes.POINTER(CSRDesc),
@@ -469,6 +471,15 @@ def count(lat, tab, q: Queries, buf: QueryBuffers, launch: LaunchConfig | None =
     cs = buf.c()
     check(load().sphidx_count(lat.handle, tab.handle if tab else None, ctypes.byref(q), ctypes.byref(cs),
                               ctypes.byref(ln), _stream(stream)), "count")
+
+
+def count_kernel(lat, tab, q: Queries, buf: QueryBuffers, launch: LaunchConfig | None = None) -> str | None:
+    """The kernel that `count` takes for these arguments (None: refused)."""
+    ln = (launch or LaunchConfig()).c()
+    cs = buf.c()
+    name = load().sphidx_count_kernel(lat.handle, tab.handle if tab else None, ctypes.byref(q), ctypes.byref(cs),
+                                      ctypes.byref(ln))
+    return name.decode() if name else None
 
 
 def stream_status(stream=None):
