@@ -81,10 +81,16 @@ def time_config(run_once, reps=3):
     return ts[len(ts) // 2]
 
 
+TILES = "tile_count_kernel"
+
+
 def candidates(schedule):
     if schedule == sphidx.SCHED_PERSISTENT:
+        # groups and one query per wavefront, each asked for: left to the
+        # library's choice a candidate would time one of the two again
+        yield dict(waves_per_block=4, tile=64, blocks_per_cu=8, sort_cap=256, table_in_lds=0, interior=1, grouped=1)
         for w, t, b, c, l, i, g in itertools.product((2, 4), (16, 64, 256), (4, 6, 8), (128, 256), (0, 1, 2), (1, 2),
-                                                     (0, 1)):
+                                                     (1, 2)):
             yield dict(waves_per_block=w, tile=t, blocks_per_cu=b, sort_cap=c, table_in_lds=l, interior=i,
                        grouped=g)
     else:
@@ -93,21 +99,33 @@ def candidates(schedule):
 
 
 def tune(shape: dict, make_runner, method=sphidx.METHOD_SPHERE, schedule=sphidx.SCHED_PERSISTENT,
-         use_cache=True, save=True, log=None, subcell_runner=None, subcell_bits=(0, 1, 2, 3)):
+         use_cache=True, save=True, log=None, subcell_runner=None, subcell_bits=(0, 1, 2, 3), kernel_of=None):
     """make_runner(LaunchConfig) -> callable that runs one query pass set.
     Returns the best LaunchConfig fields as a dict.  With subcell_runner
     ((LaunchConfig, s) -> callable running the same passes with tables of s
     sub-cell bits per axis), the launch is searched first and the sub-cell
     bits then, with that launch; the result then holds "subcell_bits" too
-    (not a LaunchConfig field: the caller builds its tables with it)."""
+    (not a LaunchConfig field: the caller builds its tables with it).  With
+    kernel_of (LaunchConfig -> the count kernel it takes, sphidx.count_kernel),
+    launches counted by tiles, which use none of these fields, are timed once,
+    with the library's default shape, and keep it."""
     arch = _arch()
     key = _key(arch, dict(shape, method=method, schedule=schedule))
     cache = load_cache()
     if use_cache and key in cache:
         return cache[key]["config"]
-    best = None
+    best, tiles_done = None, False
+
+    def by_tiles(cfg):
+        return kernel_of is not None and kernel_of(
+            sphidx.LaunchConfig(method=method, schedule=schedule, **cfg)) == TILES
+
     for cfg in candidates(schedule):
         ln = sphidx.LaunchConfig(method=method, schedule=schedule, **cfg)
+        if by_tiles(cfg):
+            if tiles_done:
+                continue
+            tiles_done = True
         try:
             ms = time_config(make_runner(ln))
         except sphidx.SphidxError as err:  # e.g. the row table does not fit in LDS
@@ -126,8 +144,8 @@ def tune(shape: dict, make_runner, method=sphidx.METHOD_SPHERE, schedule=sphidx.
         return {}
     # waves per long radius row (one block per row in the write pass; 1:
     # one wave per row, windowed), with the launch found above
-    best_lw = None
-    for lw in (1, 2, 4, 8):
+    best_lw, tiles = None, by_tiles(best[1])
+    for lw in () if tiles else (1, 2, 4, 8):
         cfg = dict(best[1], long_row_waves=lw)
         try:
             ms = time_config(make_runner(sphidx.LaunchConfig(method=method, schedule=schedule, **cfg)))
@@ -141,7 +159,7 @@ def tune(shape: dict, make_runner, method=sphidx.METHOD_SPHERE, schedule=sphidx.
             best_lw = (ms, cfg)
     if best_lw is not None:
         best = best_lw
-    if subcell_runner is not None:
+    if subcell_runner is not None and not tiles:
         ln = sphidx.LaunchConfig(method=method, schedule=schedule, **best[1])
         best_s = None
         for sb in subcell_bits:
@@ -158,7 +176,8 @@ def tune(shape: dict, make_runner, method=sphidx.METHOD_SPHERE, schedule=sphidx.
         if best_s is not None:
             best = (best_s[0], dict(best[1], subcell_bits=best_s[1]))
     if save:
-        cache = load_cache()
+        # (entries of other sources are of no use: dropped)
+        cache = {k: v for k, v in load_cache().items() if k.split("|")[1] == kernel_version()}
         cache[key] = {"config": best[1], "ms": best[0]}
         tmp = CACHE + ".tmp"
         with open(tmp, "w") as f:
