@@ -181,7 +181,7 @@ def host_info():
     return {"cpu_model": model, "logical_cpus": os.cpu_count()}
 
 
-def tuned_config(args, shape, make_runner, method=None, schedule=None, subcell_runner=None):
+def tuned_config(args, shape, make_runner, method=None, schedule=None, subcell_runner=None, kernel_of=None):
     """(launch fields, sub-cell bits of the tables): tuned on the device, or
     from the cache with --no-tune (2 sub-cell bits when none was tuned)."""
     from paper_cs_0608108_amd import autotune, sphidx
@@ -191,7 +191,7 @@ def tuned_config(args, shape, make_runner, method=None, schedule=None, subcell_r
         cfg = autotune.cached(shape, method, schedule)
     else:
         cfg = autotune.tune(shape, make_runner, method=method, schedule=schedule, log=log,
-                            subcell_runner=subcell_runner)
+                            subcell_runner=subcell_runner, kernel_of=kernel_of)
     cfg = dict(cfg)
     return cfg, int(cfg.pop("subcell_bits", 2))
 
@@ -246,11 +246,13 @@ def leg_timestep(args, out):
             sphidx.write(sim.lat, tabs[sb], sim.q, sim.buf, ln)
         return run
 
-    cfg, sbits = tuned_config(args, shape, query_step, subcell_runner=subcell_step)
+    cfg, sbits = tuned_config(args, shape, query_step, subcell_runner=subcell_step,
+                              kernel_of=lambda ln: sphidx.count_kernel(sim.lat, sim.tab, sim.q, sim.buf, ln))
     sim.tab = tabs[sbits] if sbits in tabs else sphidx.Tables(sim.lat, sbits, r)
     tabs.clear()
     sim.launch = sphidx.LaunchConfig(method=sphidx.METHOD_SPHERE, schedule=sphidx.SCHED_PERSISTENT, **cfg)
-    log(f"timestep launch config: {cfg}, sub-cell bits {sbits}")
+    kernel = sphidx.count_kernel(sim.lat, sim.tab, sim.q, sim.buf, sim.launch)
+    log(f"timestep launch config: {cfg}, sub-cell bits {sbits}, {kernel}")
     # the dominant kernel's duration: eager steps (the same kernels and
     # arguments the graph replays) with HIP events the library records
     # around the count kernel on the launch stream
@@ -426,8 +428,7 @@ def leg_timestep(args, out):
     alg = query_bytes(n, ncells, n, pairs)
     upd = resident_update_bytes(n, ncells)
     step_alg = upd["move"] + upd["rebuild"] + alg
-    rl = roofline(w.name, ("tile_count_kernel" if cfg.get("grouped") else "count_kernel")
-                  + " (walk, test, sort, keep rows)", alg, kern_ms, out.get("hbm_copy_GBps"),
+    rl = roofline(w.name, kernel + " (walk, test, sort, keep rows)", alg, kern_ms, out.get("hbm_copy_GBps"),
                   {"step": {"algorithmic_bytes": int(step_alg), "ms": round(ms, 4),
                             "achieved": round(step_alg / (ms * 1e-3) / 1e9, 2),
                             "frac": round(step_alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 5),
@@ -585,7 +586,8 @@ def leg_c2(args, out):
             sphidx.write(lat, tabs[sb], q, buf, ln)
         return run
 
-    cfg, sbits = tuned_config(args, shape, lambda ln: (lambda: step(ln)), subcell_runner=subcell_step)
+    cfg, sbits = tuned_config(args, shape, lambda ln: (lambda: step(ln)), subcell_runner=subcell_step,
+                              kernel_of=lambda ln: sphidx.count_kernel(lat, tab, q, buf, ln))
     tab = tabs[sbits] if sbits in tabs else sphidx.Tables(lat, sbits, rmax)
     tabs.clear()
     tuned = sphidx.LaunchConfig(method=sphidx.METHOD_SPHERE, schedule=sphidx.SCHED_PERSISTENT, **cfg)
@@ -680,7 +682,7 @@ def leg_c2(args, out):
         # the paper's own table design (64 specialised cell tables, Eq. 1
         # run-time test), one query per wavefront, against the row tables in
         # the same launch shape
-        one = dataclasses.replace(tuned, grouped=0)
+        one = dataclasses.replace(tuned, grouped=2)
         ms_one, _, k_one = timed(one, k2, 1)
         ms_p64, _, k_p64 = timed(sphidx.LaunchConfig(method=sphidx.METHOD_PAPER64, schedule=sphidx.SCHED_PERSISTENT,
                                                      **{k_: v for k_, v in cfg.items()
@@ -771,8 +773,8 @@ def leg_c2(args, out):
         "phase_ms": {"rebuild": round(float(phases[0]), 4), "count": round(float(phases[1]), 4),
                      "write": round(float(phases[2]), 4)},
         "bit_exact_vs_oracle": exact,
-        "roofline": roofline(w.name, ("group_count_kernel" if cfg.get("grouped") else "count_kernel")
-                             + " (walk, test, sort, keep rows)", alg, float(kern[0]), out.get("hbm_copy_GBps"),
+        "roofline": roofline(w.name, sphidx.count_kernel(lat, tab, q, buf, tuned) + " (walk, test, sort, keep rows)",
+                             alg, float(kern[0]), out.get("hbm_copy_GBps"),
                              {"write_pass_ms": round(float(kern[1]), 4),
                               "library_overhead_bytes": overhead_bytes(n, total)}),
         "cpu_baseline": cpu,
@@ -826,7 +828,8 @@ def leg_knn(args, out):
             sphidx.write(lat, tabs[sb], q, buf, ln_)
         return run
 
-    cfg, sbits = tuned_config(args, shape, step_with, subcell_runner=subcell_step)
+    cfg, sbits = tuned_config(args, shape, step_with, subcell_runner=subcell_step,
+                              kernel_of=lambda ln: sphidx.count_kernel(lat, tab, q, buf, ln))
     tab = tabs[sbits] if sbits in tabs else sphidx.Tables(lat, sbits, cap)
     tabs.clear()
     ln = sphidx.LaunchConfig(**cfg)
@@ -917,7 +920,7 @@ def leg_knn(args, out):
                 "step": "rebuild + K-NN count + scan + write (top-K rows, sorted by (dist2, id))",
                 "pairs_per_step": pairs,
                 "sampled_rows_bit_exact_vs_oracle": exact,
-                "roofline": roofline(w.name, ("group_count_kernel" if cfg.get("grouped") else "count_kernel")
+                "roofline": roofline(w.name, sphidx.count_kernel(lat, tab, q, buf, ln)
                                      + " (K-NN rows searched, sorted and kept)", alg, kern_ms,
                                      out.get("hbm_copy_GBps"),
                                      {"library_overhead_bytes": overhead_bytes(n, pairs)}),
