@@ -2892,17 +2892,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void ti
 // ---------------------------------------------------------------------------
 // Pass 1, radius rows that fit the LDS buffer: collect, sort, store.
 
-// BARE: what it does with rows of tiles, which have no descriptor (tile_query).
+// TILES: the walk list may hold rows of tiles, which have no descriptor
+// (tile_query); the kernel then has a copy of the row's code for each source.
 // One query from either source was held in vector registers, 77 instead of 52,
-// and a kernel with both costs short-lived waves more to start, so a call whose
-// count pass cannot have used tiles takes the kernel without (kNoBare); the
-// persistent schedule, both in one, each with its copy of the row's code
-// (kBoth); the plain schedule, the kernel without and a second launch for
-// those rows (kBareOnly).  Rows without a stash, write pass, ms, one query from
-// either source and now: 1,048,576 uneven radii 1.07 -> 0.97, plain launch
-// 1.41 -> 1.34; r = 3 cells 1.25 -> 1.11, plain launch 1.32 -> 1.22.
-enum { kNoBare = 0, kBoth = 1, kBareOnly = 2 };
-template <int METHOD, bool TLDS, bool FROM_LIST, int BARE>
+// and a kernel with both costs short-lived waves more to start, so only the
+// persistent schedule takes it in one launch, and only where the count pass can
+// have used tiles (A.tiles).  The plain schedule takes the kernel without, which
+// leaves such a walk list to a second launch (A.tiles 2).  Rows without a stash,
+// write pass, ms, one query from either source and now: 1,048,576 uneven radii
+// 1.07 -> 0.97; r = 3 cells 1.25 -> 1.11, plain launch 1.32 -> 1.22.
+template <int METHOD, bool TLDS, bool FROM_LIST, bool TILES>
 __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs A) {
     extern __shared__ __align__(16) char smem[];
     const uint32_t* tab_lds = stage_table<TLDS>(T, smem);
@@ -2925,11 +2924,9 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
     // the main launch takes the walk list, the list launch skips kept rows
     const bool stashed = A.stash_hdr[kHdrMode] != 0u;
     const bool from_walk = !FROM_LIST && stashed;
-    // rows of tiles: positions below `tiled`, in the region (A.tiles: the
-    // count pass may have used them)
-    const uint32_t tiled =
-        !FROM_LIST && A.tiles && from_walk && uni(A.stash_hdr[kHdrTiles]) != 0u ? uni(L.cs[L.ncells]) : 0u;
-    if (BARE == kBareOnly && tiled == 0u) return;
+    const bool of_tiles = !FROM_LIST && A.tiles && from_walk && uni(A.stash_hdr[kHdrTiles]) != 0u;
+    if (TILES ? A.tiles == 2u && !of_tiles : of_tiles) return;
+    const uint32_t tiled = TILES && of_tiles ? uni(L.cs[L.ncells]) : 0u;  // rows of tiles: positions below, in the region
     const uint32_t idbits = L.n > 1 ? 32u - (uint32_t)__builtin_clz(L.n - 1u) : 0u;  // ids are below n
     const uint32_t nq = FROM_LIST ? uni(*A.list_count) : (from_walk ? uni(*A.walk_count) : A.Q);
     auto write_row = [&](const Query& s, uint32_t qi, auto from_tile) __attribute__((always_inline)) {
@@ -2981,11 +2978,13 @@ __global__ __launch_bounds__(256) void write_kernel(LatArgs L, TabArgs T, QArgs 
     for_each_query(nq, A, queue_set(A, FROM_LIST ? (int)A.list_set : (from_walk ? kQWalk : kQWrite)),
                    [&](uint32_t ti_) {
         const uint32_t qi = FROM_LIST ? uni(A.list[ti_]) : (from_walk ? uni(A.walkq[ti_]) : ti_);
-        if (qi < tiled) {
-            if constexpr (BARE != kNoBare) write_row(tile_query(L, T, A, qi), qi, std::true_type());
-        } else {
-            if constexpr (BARE != kBareOnly) write_row(load_query(L, A, qi), qi, std::false_type());
+        if constexpr (TILES) {
+            if (qi < tiled) {
+                write_row(tile_query(L, T, A, qi), qi, std::true_type());
+                return;
+            }
         }
+        write_row(load_query(L, A, qi), qi, std::false_type());
     });
 }
 
@@ -4020,21 +4019,24 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
                            q.Q >= kTileMinQ
                        ? 1u
                        : 0u;
+        auto with_tiles = [&]() {
+            return launch_ptr(either ? SPHIDX_PICKS(write_kernel, variant, kEither, , false, true)
+                                     : SPHIDX_PICKS(write_kernel, variant, kSphere, , false, true),
+                              q.Q, qw, w, b, sh1, st, L, T);
+        };
         if (qw.tiles && q.persistent)
-            e = launch_ptr(either ? SPHIDX_PICKS(write_kernel, variant, kEither, , false, kBoth)
-                                  : SPHIDX_PICKS(write_kernel, variant, kSphere, , false, kBoth),
-                           q.Q, qw, w, b, sh1, st, L, T);
+            e = with_tiles();
         else
-            e = launch_ptr(either ? SPHIDX_PICK(write_kernel, variant, kEither, , false, kNoBare)
-                                  : SPHIDX_PICKP(write_kernel, variant, kSphere, , false, kNoBare),
+            e = launch_ptr(either ? SPHIDX_PICK(write_kernel, variant, kEither, , false, false)
+                                  : SPHIDX_PICKP(write_kernel, variant, kSphere, , false, false),
                            q.Q, qw, w, b, sh1, st, L, T);
         if (e == hipSuccess && qw.tiles && !q.persistent) {
             // (resident waves from the walk list's queues, which the copy has
             // cleared: a grid of a wave per query took 65 us to find nothing)
             qw.persistent = 1u;
             qw.tile = 64u;
-            e = launch_ptr(SPHIDX_PICKS(write_kernel, variant, kSphere, , false, kBareOnly), q.Q, qw, w, b, sh1, st, L,
-                           T);
+            qw.tiles = 2u;
+            e = with_tiles();
         }
         if (e == hipSuccess) e = mark(ev_end);
         if (e != hipSuccess) return e;
@@ -4042,7 +4044,7 @@ hipError_t launch_query_pass(int pass, const LatArgs& L, const TabArgs& T, const
             ql.list = q.fbq;
             ql.list_count = q.fb_count;
             ql.list_set = kQFbWrite;
-            e = launch_ptr((const void*)write_kernel<kCube, false, true, kNoBare>, 0, ql, w, b,
+            e = launch_ptr((const void*)write_kernel<kCube, false, true, false>, 0, ql, w, b,
                            query_lds_bytes(1, q.sort_cap, w, 0), st, L, T);
             if (e != hipSuccess) return e;
         }

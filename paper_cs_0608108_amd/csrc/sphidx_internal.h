@@ -168,7 +168,8 @@ struct QArgs {
     uint32_t knn_rev;   // volume choice: K-NN queries below this take the cube
     uint32_t model;     // volume choice: 0 = cells, 1 = estimated lane work
     uint32_t* method_out;  // optional per query row: the walk used
-    uint32_t tiles;        // count pass: the tile kernel counts, so only rows it does not keep get descriptors
+    uint32_t tiles;        // count pass: the tile kernel counts and keeps rows, which get no descriptors; write pass: it
+                           // may have (1), and this launch is for the rows that it did not keep (2)
     uint32_t merged;       // the main kernels take the fallback queries themselves (small batches)
     uint32_t long_waves;   // write pass: waves per long radius row (one block each); <= 1: one wave, windowed
 };
