@@ -263,7 +263,8 @@ typedef struct {
  * each radius row of at most sort_cap objects, each longer one that a block
  * counts (long_row_waves), and each K-NN row of K <= 64 (searched there to
  * the end), already sorted, so that the write pass copies it into place
- * instead of walking the tables again.  A row needs 4 bytes per object (12 when the count call passes dist2_dev).
+ * instead of walking the tables again.  A row needs 4 bytes per object (12 when
+ * the count call passes dist2_dev).
  * Rows that do not fit are walked again by the write pass, so any size is
  * correct; sphidx_query_stash_bytes gives the size that keeps every row.
  * The write pass must use the workspace the count pass used, unchanged.
@@ -302,8 +303,9 @@ typedef struct {
     uint32_t waves_per_block; /* 1, 2 or 4; 0 = default (4) */
     uint32_t tile;            /* queries per wave slice / per queue grab; 0 = default */
     uint32_t blocks_per_cu;   /* persistent residency; 0 = default */
-    uint32_t sort_cap;        /* per-wave LDS row buffer (64, 128 or 256); longer rows take the
-                                 windowed top-M path; 0 = 256 */
+    uint32_t sort_cap;        /* per-wave LDS row buffer (64, 128 or 256); longer radius rows go one
+                                 block each (long_row_waves), longer K-NN rows through windows of
+                                 it; 0 = 256 */
     uint32_t table_in_lds;    /* 1: stage the whole row table in LDS (CAPACITY if it does not fit);
                                  2: stage in chunks: the first rows of every (y, z) class table, as
                                  many as fit the LDS beside the passes' buffers (CAPACITY below 16),
@@ -323,9 +325,11 @@ typedef struct {
                             recorded when Q = 0) */
     uint32_t no_stash;   /* 1: never keep rows in the workspace stash (see sphidx_csr) */
     uint32_t grouped;    /* 1: the count pass takes radius queries in groups of several per
-                            wavefront (persistent schedule), and K-NN queries of the sphere
-                            tables with 2K <= sort_cap as radius rows at a first search
-                            radius (expected to hold min(1.7K, K + 3 sqrt(K) + 3) objects),
+                            wavefront (persistent schedule; all-agents queries of one
+                            radius, from 1,024 on, by tiles of space where their expected
+                            rows suit), and K-NN queries of the sphere tables with
+                            2K <= sort_cap as radius rows at a first search radius
+                            (expected to hold min(1.7K, K + 3 sqrt(K) + 3) objects),
                             keeping the first K when it holds K (rows short of K are searched
                             again in groups at a larger radius, then one query per
                             wavefront; the stash needs K pairs per such row);

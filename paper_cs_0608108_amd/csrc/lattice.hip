@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_down_kernel(const T* in, T*
 // Short arrays in one launch: one block takes the chunks of kScanBlock
 // elements in order, carrying the running total (each chunk is read whole
 // before any of it is written, so the scan can be in place).  A query batch
-// of a few thousand rows then costs one launch instead of three.
+// of a few thousand rows then costs one launch instead of two.
 constexpr uint32_t kScanSingleChunks = 4;
 
 template <typename T>

@@ -2218,14 +2218,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void g
 // one bucket sort, its keys held in registers and put in place, orders the
 // group's rows.
 //
-// Bound by instruction issue (VALU 66 % busy on the 8.4 M-agent timestep, the
-// rest waits on LDS at the 12 wavefronts a CU holds).  Against a row walk per
+// Bound by instruction issue (VALU 68 % busy on the 8.4 M-agent timestep, the
+// rest waits on LDS at the 12 wavefronts a CU holds) and by what crosses the L2
+// (13.5 GB, three quarters of a copy's rate).  Against a row walk per
 // query (group_count_kernel) a query pays a sixteenth of its group's rows and
 // candidate loads, and a pair a comparison instead of an address search, three
 // wrapped differences and three products; in exchange it is tested against
 // the whole group's candidates (about 310 for 57 hits at r = 3 cells and 0.5
-// objects per cell, instead of 109).  There: 172 VALU instructions per query
-// instead of 371, count kernel 5.60 -> 3.35 ms.  With the ring holding
+// objects per cell, instead of 109).  There: 171 VALU instructions per query
+// instead of 371, count kernel 5.60 -> 3.61 ms.  With the ring holding
 // doubles, hits placed one by one, ranks from loops over each key's bucket and
 // the descriptors read it took 6.0 ms; 128-register variants spill (5.3 ms),
 // groups of 8 queries took the same time at twice the rows.
@@ -3306,7 +3307,7 @@ __device__ void block_sort_store(uint64_t* kb, uint32_t* side, uint32_t* ctl, ui
 // traffic.  Before, every such row took one window of sort_cap pairs after
 // another on one wavefront, each window walking the whole row again: 512 rows
 // of about 20,000 pairs (20 objects per cell, 7 cells, clipped 32^3) took
-// 103 ms in all; now 0.65 ms.
+// 103 ms in all; now 0.59 ms.
 // Keys (block_sort_store) hold a shell's distances from its first bucket's on,
 // so they pack far beyond a whole row's; WIDE where so few buckets pack that
 // shells would be cut by them and not by their pairs (shells_wide): 512 rows of
@@ -3427,7 +3428,7 @@ __device__ bool shell_row(const LatArgs& L, const TabArgs& T, const QArgs& A, co
 // A row is a chain of barriers with little work between them, so rows in flight
 // are what counts: 12 bytes of LDS per pair (keys, bucket counts) let four
 // blocks share a CU, where pairs with an index each, 20 bytes, let two: 16,400
-// rows of about 1,100 pairs (a service's batch of 65,536) took 528 us.
+// rows of about 1,100 pairs (a service's batch of 65,536) 528 -> 475 us.
 // (Registers for the blocks that the LDS leaves room for: four per CU are W
 // wavefronts per SIMD.)
 template <int METHOD, bool COUNT, int W>

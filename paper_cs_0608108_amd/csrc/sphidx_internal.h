@@ -129,7 +129,8 @@ struct QArgs {
     int64_t capacity;
     uint32_t* queues;   // work counters: NQSETS x NQUEUE, then the list counters
     uint32_t* long_count;
-    uint32_t* longq;    // rows handed from the write kernels to the top-M kernel
+    uint32_t* longq;    // rows handed from the write kernels to the block-per-row and top-M kernels (in the count
+                        // pass: the tile kernel's items, or a grouped count's K-NN rows for one query per wavefront)
     uint32_t* fb_count;
     uint32_t* fbq;      // sphere method: queries the tables do not cover (cube scan)
     uint32_t* walk_count;
@@ -140,7 +141,7 @@ struct QArgs {
     uint32_t* lq;       // stash mode: radius rows expected to be long, counted one block per row
     uint32_t* big_count;
     uint32_t* bigq;     // stash mode: rows not kept that go to the block-per-row and top-M kernels
-    uint32_t* item_count;  // tile count: its work items (kept in longq, free until later launches)
+    uint32_t* item_count;  // tile count: its work items (in longq)
     uint32_t* soff;     // stash mode: per output row, first stash element of its sorted row
     uint32_t* stash_hdr;  // stash header written by the count pass (see StashHdr)
     uint32_t* stash_ctr;  // NQUEUE per-region allocation counters

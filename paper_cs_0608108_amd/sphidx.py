@@ -364,7 +364,7 @@ class LaunchConfig:
     knn_reversal_fx: int = 0
     select_model: int = 0  # 0: compare cells (the paper); 1: compare estimated lane work
     method_out: torch.Tensor | None = None  # int32[Q]: the walk each query used
-    long_row_waves: int = 0  # waves per long radius row in the write pass (0 = 4, 1 = one wave, windowed)
+    long_row_waves: int = 0  # waves per long radius row (0 = 4, 1 = one wave, windowed)
 
     def c(self) -> LaunchDesc:
         d = LaunchDesc()

@@ -56,3 +56,18 @@ def test_count_kernel_names(sx):
         if stash:
             assert left["tiles"] == (want == T), (want, left)
     del uneven, cen
+
+
+def test_tile_worlds_go_by_tiles(sx):
+    """The worlds that the tile kernel's rows are compared with the oracle on
+    are counted by it."""
+    from test_gpu_tiles import WORLDS, _lat, _points
+    for world, (log2, F, mask, n, rc) in enumerate(WORLDS):
+        pts = _points(np.random.default_rng(40 + world), world)
+        r = int(rc * (1 << F))
+        lat = _lat(sx, log2, F, mask, pts, xorder=(world % 2 == 1))
+        tab = sx.Tables(lat, 2, r)
+        q = sx.make_queries(n, None, r)
+        for stash in (0, 1 << 24):
+            buf = sx.QueryBuffers(n, 0, stash_pairs=stash)
+            assert sx.count_kernel(lat, tab, q, buf, sx.LaunchConfig(grouped=1, interior=1)) == "tile_count_kernel", world
