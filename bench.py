@@ -828,30 +828,36 @@ def leg_knn(args, out):
             sphidx.write(lat, tabs[sb], q, buf, ln_)
         return run
 
+    # the order of the objects inside a cell: the counting sort's, or by x
+    # (rows over dense cells then narrowed to the sphere's x-slab); the
+    # faster of the two, each over a few steps
+    def pick_order(launch):
+        order_ms = {}
+        for order in (sphidx.ORDER_ANY, sphidx.ORDER_X):
+            lat.set_cell_order(order)
+            for _ in range(2):
+                step_with(launch)()
+            torch.cuda.synchronize()
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(5):
+                step_with(launch)()
+            e1.record()
+            torch.cuda.synchronize()
+            order_ms["x" if order == sphidx.ORDER_X else "any"] = round(e0.elapsed_time(e1) / 5, 4)
+        order = sphidx.ORDER_X if order_ms["x"] < order_ms["any"] else sphidx.ORDER_ANY
+        lat.set_cell_order(order)
+        return order, order_ms
+
+    # (the launch is searched in the order that the default one is faster in)
+    pick_order(sphidx.LaunchConfig())
     cfg, sbits = tuned_config(args, shape, step_with, subcell_runner=subcell_step,
                               kernel_of=lambda ln: sphidx.count_kernel(lat, tab, q, buf, ln))
     tab = tabs[sbits] if sbits in tabs else sphidx.Tables(lat, sbits, cap)
     tabs.clear()
     ln = sphidx.LaunchConfig(**cfg)
     log(f"knn launch config: {cfg}, sub-cell bits {sbits}")
-    # the order of the objects inside a cell: the counting sort's, or by x
-    # (rows over dense cells then narrowed to the sphere's x-slab); the
-    # faster of the two, each over a few steps
-    order_ms = {}
-    for order in (sphidx.ORDER_ANY, sphidx.ORDER_X):
-        lat.set_cell_order(order)
-        for _ in range(2):
-            step_with(ln)()
-        torch.cuda.synchronize()
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        e0.record()
-        for _ in range(5):
-            step_with(ln)()
-        e1.record()
-        torch.cuda.synchronize()
-        order_ms["x" if order == sphidx.ORDER_X else "any"] = round(e0.elapsed_time(e1) / 5, 4)
-    order = sphidx.ORDER_X if order_ms["x"] < order_ms["any"] else sphidx.ORDER_ANY
-    lat.set_cell_order(order)
+    order, order_ms = pick_order(ln)
     log(f"knn cell order: {order_ms} ms/step -> {'x' if order else 'any'}")
     for _ in range(2):
         step_with(ln)()
