@@ -67,3 +67,59 @@ def test_sparse_rows_match_oracle(sx, orc, log2, mask, clustered, k, groups):
         alone = left["extra"] in (0, left["fallback"]) and left["long"] <= left["fallback"]
         assert groups is None or alone == (ln.grouped == 2 or (ln.grouped == 0 and not groups)), left
     del kd
+
+
+@pytest.mark.parametrize("clustered", [0.0, 0.7])
+def test_sampled_mixed_batches_and_replays(sx, orc, clustered):
+    """A mixed batch (radius and K-NN rows) whose path the sample chooses, and
+    one captured graph replayed while the objects change from sparse to
+    clustered and back: every replay as the oracle has it."""
+    import torch
+    log2, F, n = (7, 6, 7), 12, 66000
+    rng = np.random.default_rng(int(clustered * 10) + 5)
+    W = [1 << (log2[a] + F) for a in range(3)]
+
+    def cloud(share):
+        pts = [rng.integers(0, W[a], n) for a in range(3)]
+        m = int(share * n)
+        if m:
+            centre = rng.integers(0, 24, m)
+            for a in range(3):
+                pts[a][:m] = (rng.integers(0, W[a], 24)[centre] + rng.normal(0, 2 << F, m).astype(np.int64)) % W[a]
+        return tuple(p.astype(np.uint32) for p in pts)
+
+    cap = 5 << F
+    r = np.where(np.arange(n) % 3 == 0, rng.integers(1, 2 << F, n), cap).astype(np.uint32)
+    k = np.where(np.arange(n) % 3 == 0, 0, rng.integers(1, 40, n)).astype(np.uint32)
+    rd, kd = sx.to_dev_u32(r), sx.to_dev_u32(k)
+    lat = sx.Lattice(log2, F, 7, n)
+    tab = sx.Tables(lat, 1, cap)
+    dev = [sx.to_dev_u32(p) for p in cloud(clustered)]
+    q = sx.make_queries(n, None, rd, kd, sx.MODE_MIXED)
+    buf = sx.QueryBuffers(n, 4_000_000, stash_pairs=4_000_000)
+    lat.build(*dev)
+    name = sx.count_kernel(lat, tab, q, buf)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        lat.build(*dev)
+        sx.query(lat, tab, q, buf)
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            lat.build(*dev)
+            sx.query(lat, tab, q, buf)
+    torch.cuda.synchronize()
+    for share in (clustered, 0.7 - clustered, clustered, 0.7 - clustered):
+        pts = cloud(share)
+        for d, p in zip(dev, pts):
+            d.copy_(sx.to_dev_u32(p))
+        graph.replay()
+        torch.cuda.synchronize()
+        g = orc.Grid(orc.Lattice(log2, F, 7), pts)
+        ref = g.mixed(k, r)
+        g.close()
+        assert len(ref.ids) <= 4_000_000
+        say(f"sampled mixed replay share={share} kernel={name} pairs={len(ref.ids)}")
+        assert_same(buf.host(), ref, f"share {share}")
+    del rd, kd
